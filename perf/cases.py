@@ -380,7 +380,9 @@ def prepare(c, seed):
         torch.cuda.synchronize()
         return s
     U = _field(dims, seed, DEV)
-    s.gid = s.ctx.set_gauge(_canonical_links(U), _kappa(c), c["csw"])
+    links = _canonical_links(U)
+    torch.cuda.synchronize()   # set_gauge takes no stream: the links have to be there
+    s.gid = s.ctx.set_gauge(links, _kappa(c), c["csw"])
     s.t0, s.t1 = c["t0"], c["t1"]
     if s.kind == "level1":
         s.args = (BETA, 1601004 + seed, 1003, c["nsweeps"], c["n_or"])
