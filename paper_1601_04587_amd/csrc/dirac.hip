@@ -841,10 +841,17 @@ static hipError_t hop_batch_impl(const SlotDesc<T2>* slots, const int* tile_star
                                  const int* nslots_p, int nrhs, int R, int mode, int red, int fin, int faux, int fout,
                                  int fred, int par_out, int grid, int order, int splits, int stage,
                                  hipStream_t st) {
-  // nw waves cover the columns of a tile; they are split into ng blocks of W waves
+  // nw waves cover the columns of a tile; they are split into ng blocks of W
+  // waves.  A staged, unsplit workgroup always has the most waves its kernel
+  // is built for: those beyond the columns only copy links and clover data,
+  // which one wave does 58 pairs of in turn (M-hat pair of 24^3 x 16 with 1,
+  // 3 and 10 columns: FP32 0.225, 0.142 and 0.217 ms without them, 0.093,
+  // 0.106 and 0.194 with; FP64 0.459, 0.283 and 0.478, then 0.188, 0.216 and
+  // 0.477).
   const int nw = (nrhs + R - 1) / R;
   if (splits < 1 || splits > nw) return hipErrorInvalidValue;
-  const int W = (nw + splits - 1) / splits, ng = (nw + W - 1) / W;
+  const int W = stage && splits == 1 ? (kMaxRhs + R - 1) / R : (nw + splits - 1) / splits;
+  const int ng = (nw + W - 1) / W;
   const int block = 64 * W;
   if (order < 0 || order >= TILE_ORDER_NUM || (order != TILE_ORDER_LINEAR && grid % kXcd)) return hipErrorInvalidValue;
   if (stage) {
