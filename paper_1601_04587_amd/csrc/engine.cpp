@@ -140,8 +140,6 @@ void ctx_init(Ctx* c, const ddml_lattice* lat, int device, size_t budget) {
   }
   c->pool.reset(new DevPool(budget));
   c->flag = DBuf(c->pool.get(), sizeof(int));
-  c->tune16.stage = 1;  // FP32 and 16-bit fields (two-row links) are always read through the LDS staging
-  c->tune32.stage = 1;
   for (int m = 0; m < 4; ++m) {
     c->full.lo[m] = 0;
     c->full.hi[m] = lat->dims[m];
@@ -656,6 +654,18 @@ void apply_eo(Ctx* c, int gauge_id, int dom_id, const double* in, double* out, i
   }
 }
 
+// Whether the stencil of a precision stages its operator data in LDS under a
+// launch choice.  FP32 and 16-bit fields (two-row links) always do.  FP64 fields
+// do unless the choice says otherwise, but for a single column: with several,
+// every wavefront of an unstaged tile reads the links and clover data itself
+// and misses L1, with one there is nothing to share and the 116 KB of LDS
+// leave one tile per CU (M-hat pair of 24^3 x 16 unstaged and staged: 0.148
+// and 0.188 ms with 1 column, 0.267 and 0.198 with 2, 1.35 and 0.55 with 12).
+static int stage_of(int stage, int prec, int nrhs) {
+  if (prec != DDML_FP64) return 1;
+  return stage >= 0 ? stage : (nrhs > 1 ? 1 : 0);
+}
+
 // ----------------------------------------------------------- batch runner
 template <typename T2>
 BatchRunner<T2>::~BatchRunner() {
@@ -694,7 +704,7 @@ void BatchRunner<T2>::init(Ctx* c, int nrhs_, const TuneChoice& tn, int max_slot
   max_slots = max_slots_;
   order = tn.order;
   splits = std::min(tn.splits, (nrhs + R - 1) / R);
-  stage = tn.stage;
+  stage = stage_of(tn.stage, std::is_same<T2, double2>::value ? DDML_FP64 : DDML_MIXED_FP32, nrhs);
   table = DBuf(c->pool.get(), sizeof(SlotDesc<T2>) * max_slots);
   tstart = DBuf(c->pool.get(), sizeof(int) * (max_slots + 1));
   xstart = DBuf(c->pool.get(), sizeof(int) * kXcd * (max_slots + 1));
@@ -1612,7 +1622,7 @@ void time_stencil(Ctx* c, int gauge_id, int dom_id, int nrhs, int prec, int iter
   const int order = want.order >= 0 ? want.order : tn.order;
   int grid = want.grid > 0 ? want.grid : tn.grid;
   int splits = want.splits > 0 ? want.splits : tn.splits;
-  const int stage = want.stage >= 0 ? want.stage : tn.stage;
+  const int stage = want.stage >= 0 ? want.stage : stage_of(tn.stage, prec, nrhs);
   if (R < 1 || R > 3 || order >= TILE_ORDER_NUM || stage > 1)
     throw Error{DDML_EINVAL, "R must be 1..3, order 0..3 and stage 0 or 1"};
   splits = std::min(splits, (nrhs + R - 1) / R);
