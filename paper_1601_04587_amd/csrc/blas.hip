@@ -13,12 +13,16 @@
 // recursive residual by the true one r', the Krylov space is kept and only p
 // and rho are rescaled, p = r' + (rho'/rho)(p - r_old) (VEC_RELUP, FIN_RELUP,
 // VEC_PFIX); a column whose recursion broke down starts afresh instead.
-// Every kernel walks a slot table
-// (one entry per domain solve in flight) with a grid-stride loop over virtual
-// 64-site tiles; a workgroup is 64 sites x nrhs columns, one wavefront per
-// column, so every reduction is a wavefront reduction written to a fixed
-// partial slot and the final sums are taken in a fixed order: results do not
-// depend on how many solves share the launch.
+// Every kernel walks a slot table (one entry per domain solve in flight) with a
+// grid-stride loop over virtual 64-site tiles, one wavefront per column of a
+// tile, so every reduction is a wavefront reduction written to a fixed partial
+// slot and the final sums are taken in a fixed order: results do not depend on
+// how many solves share the launch.  BiCGstab's FP32 and FP64 vector steps take
+// kVecCols columns of a tile per workgroup: nothing is shared between columns,
+// and a small domain (32 tiles of 12 columns) fills 96 CUs instead of 32, whose
+// load paths were the limit (VEC_XRP 10.9 -> 6.1 us, VEC_S 6.4 -> 4.5 us; the
+// same time on 4096 tiles).  The 16-bit steps keep twelve columns: split, they
+// took 13.7 us instead of 13.3 on 256 tiles.
 #include "ddml_common.hpp"
 #include "launchers.hpp"
 
@@ -47,15 +51,24 @@ __device__ __forceinline__ double2* part_at(double2* partial, int nrhs, int ntil
   return partial + ((size_t)k * nrhs + col) * ntiles + tile;
 }
 
+// Pairs of components that VEC_XRP loads together.  The compiler keeps a load
+// behind the stores before it (the fields may alias), so pair by pair the five
+// loads of a pair would be one trip to memory each.
+template <typename T2> constexpr int kChunk = sizeof(T2) == sizeof(float2) ? 3 : 2;
+
+constexpr int kVecCols = 4;
+
 template <typename T2, int OP>
-__global__ void __launch_bounds__(768) k_vec(const SlotDesc<T2>* __restrict__ slots, const int* __restrict__ tile_start,
-                                             const int* __restrict__ nslots_p) {
+__global__ void __launch_bounds__(64 * kVecCols)
+    k_vec(const SlotDesc<T2>* __restrict__ slots, const int* __restrict__ tile_start, const int* __restrict__ nslots_p,
+          int ng) {
   using T = decltype(T2::x);
   const int ns = *nslots_p;
-  const int total = tile_start[ns];
+  const int total = tile_start[ns] * ng;
   const int lane = threadIdx.x & 63;
-  const int col = threadIdx.x >> 6;
-  for (int vt = blockIdx.x; vt < total; vt += gridDim.x) {
+  for (int item = blockIdx.x; item < total; item += gridDim.x) {
+    const int vt = item / ng;
+    const int col = (item - vt * ng) * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int s = find_slot_v(tile_start, ns, vt);
     const SlotDesc<T2>& d = slots[s];
     if (col >= d.nrhs) continue;
@@ -70,38 +83,58 @@ __global__ void __launch_bounds__(768) k_vec(const SlotDesc<T2>* __restrict__ sl
     double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);
     if (OP == VEC_S) {
       const T2 al = mk<T2>((T)st.alpha.x, (T)st.alpha.y);
-      T2 o[12];
+      T2 r[12], v[12];
 #pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        const size_t q = base + 128 * k;
-        T2 r0 = mk<T2>(0, 0), r1 = r0, v0 = r0, v1 = r0;
-        if (valid) {
-          ld2(d.f[F_R] + q, r0, r1);
-          ld2(d.f[F_V] + q, v0, v1);
+      for (int k = 0; k < 12; ++k) r[k] = v[k] = mk<T2>(0, 0);
+      if (valid) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+          ld2(d.f[F_R] + base + 128 * k, r[2 * k], r[2 * k + 1]);
+          ld2(d.f[F_V] + base + 128 * k, v[2 * k], v[2 * k + 1]);
         }
-        o[2 * k] = csub(r0, cmul(al, v0));
-        o[2 * k + 1] = csub(r1, cmul(al, v1));
-        st2(d.f[F_S] + q, o[2 * k], o[2 * k + 1]);
       }
-      shadow_dot(hb, o, s0);
+#pragma unroll
+      for (int k = 0; k < 12; ++k) r[k] = csub(r[k], cmul(al, v[k]));
+#pragma unroll
+      for (int k = 0; k < 6; ++k) st2(d.f[F_S] + base + 128 * k, r[2 * k], r[2 * k + 1]);
+      shadow_dot(hb, r, s0);
     } else if (OP == VEC_XRP) {
       if (valid) {
         const T2 al = mk<T2>((T)st.alpha.x, (T)st.alpha.y), om = mk<T2>((T)st.omega.x, (T)st.omega.y);
         const T2 be = mk<T2>((T)st.beta.x, (T)st.beta.y);
+        T2* const fx = d.f[F_X] + base;
+        T2* const fp = d.f[F_P] + base;
+        T2* const fr = d.f[F_R] + base;
+        const T2* const fs = d.f[F_S] + base;
+        const T2* const ft = d.f[F_T] + base;
+        const T2* const fv = d.f[F_V] + base;
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-          const size_t q = base + 128 * k;
-          T2 x0, x1, p0, p1, sv0, sv1, t0, t1, v0, v1;
-          ld2(d.f[F_X] + q, x0, x1);
-          ld2(d.f[F_P] + q, p0, p1);
-          ld2(d.f[F_S] + q, sv0, sv1);
-          ld2(d.f[F_T] + q, t0, t1);
-          ld2(d.f[F_V] + q, v0, v1);
-          st2(d.f[F_X] + q, cadd(x0, cadd(cmul(al, p0), cmul(om, sv0))), cadd(x1, cadd(cmul(al, p1), cmul(om, sv1))));
-          const T2 n0 = csub(sv0, cmul(om, t0)), n1 = csub(sv1, cmul(om, t1));
-          st2(d.f[F_R] + q, n0, n1);
-          st2(d.f[F_P] + q, cadd(n0, cmul(be, csub(p0, cmul(om, v0)))), cadd(n1, cmul(be, csub(p1, cmul(om, v1)))));
-          s1.x += (double)n0.x * n0.x + (double)n0.y * n0.y + (double)n1.x * n1.x + (double)n1.y * n1.y;
+        for (int k0 = 0; k0 < 6; k0 += kChunk<T2>) {
+          constexpr int N = 2 * kChunk<T2>;
+          T2 x[N], p[N], sv[N], t[N], v[N];
+#pragma unroll
+          for (int j = 0; j < kChunk<T2>; ++j) {
+            const int q = 128 * (k0 + j);
+            ld2(fp + q, p[2 * j], p[2 * j + 1]);
+            ld2(fs + q, sv[2 * j], sv[2 * j + 1]);
+            ld2(ft + q, t[2 * j], t[2 * j + 1]);
+            ld2(fv + q, v[2 * j], v[2 * j + 1]);
+            ld2(fx + q, x[2 * j], x[2 * j + 1]);
+          }
+#pragma unroll
+          for (int c = 0; c < N; ++c) {
+            x[c] = cadd(x[c], cadd(cmul(al, p[c]), cmul(om, sv[c])));
+            sv[c] = csub(sv[c], cmul(om, t[c]));
+            p[c] = cadd(sv[c], cmul(be, csub(p[c], cmul(om, v[c]))));
+            s1.x += (double)sv[c].x * sv[c].x + (double)sv[c].y * sv[c].y;
+          }
+#pragma unroll
+          for (int j = 0; j < kChunk<T2>; ++j) {
+            const int q = 128 * (k0 + j);
+            st2(fx + q, x[2 * j], x[2 * j + 1]);
+            st2(fr + q, sv[2 * j], sv[2 * j + 1]);
+            st2(fp + q, p[2 * j], p[2 * j + 1]);
+          }
         }
       }
     } else if (OP == VEC_PFIX) {
@@ -294,29 +327,43 @@ __device__ __forceinline__ double2 cmuld(double2 a, double2 b) {
 __device__ __forceinline__ bool finite2(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 __device__ __forceinline__ bool zero2(double2 a) { return a.x == 0 && a.y == 0; }
 
-// Sum of partial slot k of a column over its tiles in a fixed order: thread
-// t of the workgroup adds tiles t, t + 256, ... in turn, then a fixed tree in
-// LDS (the same for every batch the solve is in).  Every thread calls it.
+// Sums of N partial slots of a column over its tiles in a fixed order: thread
+// t of the workgroup adds tiles t, t + 256, ... in turn, then a fixed tree over
+// the wavefront's lanes and the wavefronts in order (the same for every
+// batch the solve is in).  The slots are read side by side: one after the
+// other, each with a tree in LDS of its own, the four of FIN_OMEGA took 28 us
+// on 4096 tiles instead of 16 (and the one of FIN_ALPHA 9.0 instead of 5.8; more
+// threads cost more in idle workgroups than they save).  Every thread calls it.
 constexpr int kFinThreads = 256;
-__device__ __forceinline__ double2 slot_sum(const double2* partial, int nrhs, int ntiles, int k, int col,
-                                            double2* red) {
+template <int N>
+__device__ __forceinline__ void slot_sums(const double2* partial, int nrhs, int ntiles, const int (&k)[N], int col,
+                                          double2 (&out)[N]) {
+  __shared__ double2 red[kFinThreads / 64][N];
   const int tid = threadIdx.x;
-  double2 a = make_double2(0, 0);
-  const double2* p = partial + ((size_t)k * nrhs + col) * ntiles;
+  double2 a[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) a[j] = make_double2(0, 0);
+#pragma unroll 4
   for (int t = tid; t < ntiles; t += kFinThreads) {
-    const double2 u = p[t];
-    a.x += u.x;
-    a.y += u.y;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const double2 u = *part_at(const_cast<double2*>(partial), nrhs, ntiles, k[j], col, t);
+      a[j].x += u.x;
+      a[j].y += u.y;
+    }
   }
-  red[tid] = a;
-  __syncthreads();
-  for (int off = kFinThreads / 2; off > 0; off >>= 1) {
-    if (tid < off) red[tid] = make_double2(red[tid].x + red[tid + off].x, red[tid].y + red[tid + off].y);
-    __syncthreads();
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    a[j] = wsum(a[j]);
+    if ((tid & 63) == 0) red[tid >> 6][j] = a[j];
   }
-  const double2 r = red[0];
   __syncthreads();
-  return r;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    out[j] = red[0][j];
+#pragma unroll
+    for (int w = 1; w < kFinThreads / 64; ++w) out[j] = make_double2(out[j].x + red[w][j].x, out[j].y + red[w][j].y);
+  }
 }
 
 // One workgroup per (slot, column): sum the tile partials in a fixed order,
@@ -324,7 +371,6 @@ __device__ __forceinline__ double2 slot_sum(const double2* partial, int nrhs, in
 template <typename T2, int OP>
 __global__ void __launch_bounds__(kFinThreads) k_fin(const SlotDesc<T2>* __restrict__ slots,
                                                      const int* __restrict__ nslots_p) {
-  __shared__ double2 red[kFinThreads];
   const int s = blockIdx.x, col = blockIdx.y;
   if (s >= *nslots_p) return;
   const SlotDesc<T2>& d = slots[s];
@@ -334,10 +380,28 @@ __global__ void __launch_bounds__(kFinThreads) k_fin(const SlotDesc<T2>* __restr
   if ((OP == FIN_INIT || OP == FIN_RELUP) && !init_here(d, OP == FIN_INIT ? 0 : 1)) return;
   const int nr = d.nrhs, nt = d.ntiles;
   const double2 z = make_double2(0, 0);
-  const double2 a = (OP == FIN_CHECK) ? z : slot_sum(d.partial, nr, nt, 0, col, red);
-  const double2 b = (OP == FIN_ALPHA) ? z : slot_sum(d.partial, nr, nt, 1, col, red);
-  const double2 c2 = (OP == FIN_OMEGA) ? slot_sum(d.partial, nr, nt, 2, col, red) : z;
-  const double2 c3 = (OP == FIN_OMEGA) ? slot_sum(d.partial, nr, nt, 3, col, red) : z;
+  double2 a = z, b = z, c2 = z, c3 = z;
+  if constexpr (OP == FIN_ALPHA) {
+    double2 o[1];
+    slot_sums<1>(d.partial, nr, nt, {0}, col, o);
+    a = o[0];
+  } else if constexpr (OP == FIN_CHECK) {
+    double2 o[1];
+    slot_sums<1>(d.partial, nr, nt, {1}, col, o);
+    b = o[0];
+  } else if constexpr (OP == FIN_OMEGA) {
+    double2 o[4];
+    slot_sums<4>(d.partial, nr, nt, {0, 1, 2, 3}, col, o);
+    a = o[0];
+    b = o[1];
+    c2 = o[2];
+    c3 = o[3];
+  } else {
+    double2 o[2];
+    slot_sums<2>(d.partial, nr, nt, {0, 1}, col, o);
+    a = o[0];
+    b = o[1];
+  }
   if (threadIdx.x != 0) return;
   if (OP == FIN_RELUP && st.status == 0) {
     // a = (h, r'), b = |r'|^2 for the replaced residual r'; the Krylov space is
@@ -647,13 +711,15 @@ hipError_t launch_gcr_fin(const SlotDesc<double2>* slots, const int* nslots_p, i
 template <typename T2>
 static hipError_t vec_impl(const SlotDesc<T2>* slots, const int* tile_start, const int* nslots_p, int nrhs, int op,
                            int grid, hipStream_t st) {
-  dim3 b(64 * nrhs);
+  const int ng = (nrhs + kVecCols - 1) / kVecCols;
+  const dim3 b(64 * ((nrhs + ng - 1) / ng));
+  grid *= ng;
   switch (op) {
-    case VEC_S: hipLaunchKernelGGL((k_vec<T2, VEC_S>), dim3(grid), b, 0, st, slots, tile_start, nslots_p); break;
-    case VEC_XRP: hipLaunchKernelGGL((k_vec<T2, VEC_XRP>), dim3(grid), b, 0, st, slots, tile_start, nslots_p); break;
-    case VEC_PFIX: hipLaunchKernelGGL((k_vec<T2, VEC_PFIX>), dim3(grid), b, 0, st, slots, tile_start, nslots_p); break;
-    case VEC_INIT: hipLaunchKernelGGL((k_vec<T2, VEC_INIT>), dim3(grid), b, 0, st, slots, tile_start, nslots_p); break;
-    case VEC_RELUP: hipLaunchKernelGGL((k_vec<T2, VEC_RELUP>), dim3(grid), b, 0, st, slots, tile_start, nslots_p); break;
+    case VEC_S: hipLaunchKernelGGL((k_vec<T2, VEC_S>), dim3(grid), b, 0, st, slots, tile_start, nslots_p, ng); break;
+    case VEC_XRP: hipLaunchKernelGGL((k_vec<T2, VEC_XRP>), dim3(grid), b, 0, st, slots, tile_start, nslots_p, ng); break;
+    case VEC_PFIX: hipLaunchKernelGGL((k_vec<T2, VEC_PFIX>), dim3(grid), b, 0, st, slots, tile_start, nslots_p, ng); break;
+    case VEC_INIT: hipLaunchKernelGGL((k_vec<T2, VEC_INIT>), dim3(grid), b, 0, st, slots, tile_start, nslots_p, ng); break;
+    case VEC_RELUP: hipLaunchKernelGGL((k_vec<T2, VEC_RELUP>), dim3(grid), b, 0, st, slots, tile_start, nslots_p, ng); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
