@@ -822,7 +822,7 @@ int ddml_contract_nucleon(ddml_ctx ctx, const double* terms, int nlevels, double
     const size_t bytes = (size_t)nlevels * 12 * c->V * 12 * sizeof(double2);
     StreamJoin sj(c, stream);
     Staged st = stage_in(c, terms, bytes, on_device);
-    DBuf W(c->pool.get(), (size_t)nlevels * c->V * sizeof(double2));
+    DBuf W(c->pool.get(), (size_t)nlevels * (c->V / 8) * sizeof(double2));
     DBuf o(c->pool.get(), (size_t)nlevels * T * sizeof(double2));
     DBuf d(c->pool.get(), (size_t)nlevels * T * sizeof(double2));
     DDML_HIP(launch_nucleon(reinterpret_cast<const double2*>(st.cptr), c->V, T, nlevels, W.as<double2>(),

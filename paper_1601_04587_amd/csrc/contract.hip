@@ -114,125 +114,184 @@ __device__ __forceinline__ double2 cm(double2 a, double2 b) {
 }
 __device__ __forceinline__ double2 cadd2(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
-__device__ const int kEps[6][4] = {{0, 1, 2, 1}, {1, 2, 0, 1}, {2, 0, 1, 1}, {0, 2, 1, -1}, {2, 1, 0, -1}, {1, 0, 2, -1}};
-
-// Eight sink sites per workgroup of 64 threads, eight threads per site; thread
-// q of a site takes the (abc, feg) pairs q, q + 8, ... of the 36.  The levels
-// are walked in order and S^(i) = sum_{j<=i} terms[j] is accumulated in LDS,
-// so each term is read once, with loads contiguous over (site, component) for
-// each source column.  Sites where S^(i) vanishes (outside the outermost
-// domain of the series) skip the spin algebra, which is exact: every product
-// there is zero.
+// Sixteen lanes per sink site, lane 4 r + k holding the spin component (k, r) of
+// the nine colour pairs S^{ag}; a workgroup is two wavefronts, eight sites.
+// The levels are walked in order and S^(i) = sum_{j<=i} terms[j] stays in
+// registers, so each term is read once and nothing goes through LDS; every
+// sum over spin is between lanes of one 16-lane row, where a value moves with
+// one or two DPP moves.  A quad of lanes loads a column's 192 bytes of a site as
+// three runs of 64 and sorts them into spins the same way.
 //
-// The spin algebra uses the rank-2 form of P_-: (M P_-)_{kc} = y_{k, c mod 2}
-// with y_{kj} = (M_{kj} + M_{k, j+2}) / 2, so M P_- N = y z with
-// z_{jq} = N_{jq} + N_{j+2, q}; W_N2 then needs 40 complex products per pair.
+// With C g5 = diag(s_2, s_2), (C g5 S C g5)_{kr} = St_{kr} = +-S_{k^1, r^1} (+ for
+// k = r mod 2), and P_- of rank 2 (see y, z), both traces are the same sum:
+//   W_N1 - W_N2 = sum_{ag} sum_{kr} St^{ag}_{kr} G^{ag}_{kr},
+//   G^{ag}_{kr} = sum eps^{abc} eps^{feg} [ p^{ce} S^{bf}_{kr} - sum_j y^{be}_{kj} z^{cf}_{jr} ],
+//   y_{kj} = (S_{kj} + S_{k,j+2}) / 2,  z_{jr} = S_{jr} + S_{j+2,r},  p = tr[S P_-] = sum_k y_{k, k mod 2}:
+// 126 complex products per lane instead of 57 per site for each of the 36 colour
+// terms, with no operand read twice.  Sites where S^(i) vanishes (outside the
+// outermost domain of the series) skip the algebra, which is exact: every
+// product there is zero.
+//
+// Bound by its FP64 work with two waves per SIMD, near the time of reading the
+// terms (0.75 ms at 6.1 TB/s for 3 levels of 48 x 24^3): 1.10 ms for the call,
+// 1.37 with a lane per (k, r) that loaded its own components from four columns at
+// once (80% of the time in the texture addresser), 2.59 when the 36 colour terms
+// read their operands from LDS, sites 2304 bytes apart (one bank).
 constexpr int kNucSites = 8;
-constexpr int kNucThreads = 8;
 
-__device__ __forceinline__ double2 sld(const double2* S, int al, int a, int be, int b) {
-  return S[((al * 3 + a) * 4 + be) * 3 + b];
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
 }
-// v * (+i) for even k, v * (-i) for odd k: the phase of column k of C g5 = diag(s_2, s_2)
-__device__ __forceinline__ double2 mul_ph(double2 v, int k) {
-  return (k & 1) ? make_double2(v.y, -v.x) : make_double2(-v.y, v.x);
+template <int CTRL>
+__device__ __forceinline__ double2 dpp(double2 v) {
+  return make_double2(dpp<CTRL>(v.x), dpp<CTRL>(v.y));
 }
-
-__device__ double2 nucleon_pair(const double2* S, int pair) {
-  const int* e1 = kEps[pair / 6];
-  const int* e2 = kEps[pair % 6];
-  const int a = e1[0], b = e1[1], c = e1[2];
-  const int f = e2[0], e = e2[1], g = e2[2];
-  const double sgn = (double)(e1[3] * e2[3]);
-  // X = (S^{ag})^T C g5:  X_{rk} = ph(k) S^{ag}_{k^1, r}
-  double2 X[16];
-  for (int r = 0; r < 4; ++r)
-    for (int k = 0; k < 4; ++k) X[4 * r + k] = mul_ph(sld(S, k ^ 1, a, r, g), k);
-  // W_N1 = tr[X S^{bf} C g5] tr[S^{ce} P_-]
-  double2 t1 = make_double2(0, 0);
-  for (int r = 0; r < 4; ++r)
-    for (int k = 0; k < 4; ++k) t1 = cadd2(t1, cm(X[4 * r + k], mul_ph(sld(S, k, b, r ^ 1, f), r)));
-  double2 t2 = make_double2(0, 0);
-  for (int r = 0; r < 4; ++r) {
-    const double2 u = sld(S, r, c, r & 1, e), v = sld(S, r, c, (r & 1) + 2, e);
-    t2 = make_double2(t2.x + 0.5 * (u.x + v.x), t2.y + 0.5 * (u.y + v.y));
-  }
-  const double2 w1 = cm(t1, t2);
-  // W_N2 = tr[X S^{be} P_- S^{cf} C g5] = sum_{r,k,j} X_{rk} y_{kj} z_{jr}
-  double2 y[8], z[8];
-  for (int k = 0; k < 4; ++k)
-    for (int j = 0; j < 2; ++j) {
-      const double2 u = sld(S, k, b, j, e), v = sld(S, k, b, j + 2, e);
-      y[2 * k + j] = make_double2(0.5 * (u.x + v.x), 0.5 * (u.y + v.y));
-    }
-  for (int j = 0; j < 2; ++j)
-    for (int q = 0; q < 4; ++q) {
-      const double2 u = sld(S, j, c, q ^ 1, f), v = sld(S, j + 2, c, q ^ 1, f);
-      z[4 * j + q] = mul_ph(make_double2(u.x + v.x, u.y + v.y), q);
-    }
-  double2 w2 = make_double2(0, 0);
-  for (int r = 0; r < 4; ++r)
-    for (int j = 0; j < 2; ++j) {
-      double2 v = make_double2(0, 0);
-      for (int k = 0; k < 4; ++k) v = cadd2(v, cm(X[4 * r + k], y[2 * k + j]));
-      w2 = cadd2(w2, cm(v, z[4 * j + r]));
-    }
-  return make_double2(sgn * (w1.x - w2.x), sgn * (w1.y - w2.y));
+constexpr int kQuadXor2 = 0x4E, kQuadXor3 = 0x1B;   // quad_perm: lane ^ 2, lane ^ 3
+constexpr int kQuad0 = 0x00, kQuad1 = 0x55;         // quad_perm: lane 0 or 1 of each quad
+constexpr int kRor8 = 0x128, kHalfMirror = 0x141;   // lane ^ 8, lane ^ 7 of the row
+// lane ^ 4 and lane ^ 5
+__device__ __forceinline__ double2 xor4(double2 v) { return dpp<kHalfMirror>(dpp<kQuadXor3>(v)); }
+__device__ __forceinline__ double2 xor5(double2 v) { return dpp<kHalfMirror>(dpp<kQuadXor2>(v)); }
+__device__ __forceinline__ double2 sel(bool c, double2 a, double2 b) {
+  return make_double2(c ? a.x : b.x, c ? a.y : b.y);
+}
+// acc +- a b
+__device__ __forceinline__ void mac(double2& acc, double2 a, double2 b) {
+  acc.x += a.x * b.x;
+  acc.x -= a.y * b.y;
+  acc.y += a.x * b.y;
+  acc.y += a.y * b.x;
+}
+__device__ __forceinline__ void msc(double2& acc, double2 a, double2 b) {
+  acc.x -= a.x * b.x;
+  acc.x += a.y * b.y;
+  acc.y -= a.x * b.y;
+  acc.y -= a.y * b.x;
 }
 
-// PART = false: W[level][site] per sink site.  PART = true: W[level][block],
-// the sum over the workgroup's kNucSites sites in site order (the sites of a
-// workgroup lie in one time slice: every extent is even, so L^3 is a multiple
-// of 8).
-template <bool PART>
-__global__ void __launch_bounds__(64) k_nucleon_site(const double2* __restrict__ terms, size_t V, int nlevels,
-                                                     double2* __restrict__ W) {
-  __shared__ double2 S[kNucSites][144];
-  __shared__ double2 part[64];
-  __shared__ double2 sites[kNucSites];
-  __shared__ int nz[kNucSites];
-  const size_t y0 = (size_t)blockIdx.x * kNucSites;
-  const int nsite = (int)(V - y0 < (size_t)kNucSites ? V - y0 : kNucSites);
-  const int tid = threadIdx.x;
-  const int ls = tid / kNucThreads, q = tid % kNucThreads;
-  for (int e = tid; e < kNucSites * 144; e += 64) S[e / 144][e % 144] = make_double2(0, 0);
+// This lane's part of W_N1 - W_N2 of its site.
+__device__ __forceinline__ double2 nucleon_lane(const double2 (&S)[3][3], int lane) {
+  const bool odd = (lane >> 2) & 1;                  // r mod 2
+  const bool minus = ((lane >> 2) ^ lane) & 1;       // k != r mod 2
+  double2 W = make_double2(0, 0);
+  auto St = [&](int a, int g) {
+    const double2 v = xor5(S[a][g]);
+    return minus ? make_double2(-v.x, -v.y) : v;
+  };
+  double2 ym[3][3], p[3][3];                         // y_{k, r mod 2}
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+      const double2 u = dpp<kRor8>(S[a][g]);
+      ym[a][g] = make_double2(0.5 * (S[a][g].x + u.x), 0.5 * (S[a][g].y + u.y));
+      // the quads of even r hold y_{k0} and give y_00 + y_20, those of odd r y_11 + y_31
+      const double2 t = cadd2(ym[a][g], dpp<kQuadXor2>(ym[a][g]));
+      const double2 q = sel(odd, dpp<kQuad1>(t), dpp<kQuad0>(t));
+      p[a][g] = cadd2(q, xor4(q));
+    }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+      const int b = (a + 1) % 3, c = (a + 2) % 3, f = (g + 1) % 3, e = (g + 2) % 3;
+      double2 G = make_double2(0, 0);
+      mac(G, p[c][e], S[b][f]);
+      msc(G, p[c][f], S[b][e]);
+      msc(G, p[b][e], S[c][f]);
+      mac(G, p[b][f], S[c][e]);
+      mac(W, St(a, g), G);
+    }
+  double2 yo[3][3], zm[3][3], zo[3][3];              // y_{k, 1 - r mod 2}, z_{r mod 2, r}, z_{1 - r mod 2, r}
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+      yo[a][g] = xor4(ym[a][g]);
+      const double2 z = cadd2(S[a][g], dpp<kQuadXor2>(S[a][g]));   // z_{k mod 2, r}
+      const double2 z0 = dpp<kQuad0>(z), z1 = dpp<kQuad1>(z);
+      zm[a][g] = sel(odd, z1, z0);
+      zo[a][g] = sel(odd, z0, z1);
+    }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+      const int b = (a + 1) % 3, c = (a + 2) % 3, f = (g + 1) % 3, e = (g + 2) % 3;
+      double2 G = make_double2(0, 0);
+      mac(G, ym[b][e], zm[c][f]);
+      mac(G, yo[b][e], zo[c][f]);
+      msc(G, ym[b][f], zm[c][e]);
+      msc(G, yo[b][f], zo[c][e]);
+      msc(G, ym[c][e], zm[b][f]);
+      msc(G, yo[c][e], zo[b][f]);
+      mac(G, ym[c][f], zm[b][e]);
+      mac(G, yo[c][f], zo[b][e]);
+      msc(W, St(a, g), G);
+    }
+  return W;
+}
+
+// P[level][block]: the sum over the workgroup's kNucSites sites (they lie in one
+// time slice: every extent is even, so L^3 is a multiple of 8).
+__global__ void __launch_bounds__(128, 2) k_nucleon(const double2* __restrict__ terms, size_t V, int nlevels,
+                                                    double2* __restrict__ P) {
+  __shared__ double2 part[2][2];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r = (lane >> 2) & 3, k = lane & 3;
+  const size_t y = (size_t)blockIdx.x * kNucSites + 4 * w + (lane >> 4);
+  // column 3 r + b holds S[k a][r b] at component 3 k + a; lane k of the quad
+  // loads components k, k + 4 and k + 8
+  const DDML_GLOBAL f64x2* src = (const DDML_GLOBAL f64x2*)(terms + ((size_t)3 * r * V + y) * 12 + k);
+  double2 S[3][3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) S[a][b] = make_double2(0, 0);
+  f64x2 next[3][3];
+  auto load = [&](int level) {
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        next[b][j] = __builtin_nontemporal_load(src + ((size_t)level * 12 + b) * V * 12 + 4 * j);
+  };
+  load(0);
+  bool live = false;
   for (int level = 0; level < nlevels; ++level) {
-    if (tid < kNucSites) nz[tid] = 0;
-    __syncthreads();
-    // term `level`, column col = 3 beta + b holds S[alpha a][beta b] at component 3 alpha + a
-    for (int e = tid; e < 12 * kNucSites * 12; e += 64) {
-      const int col = e / (kNucSites * 12), r = e % (kNucSites * 12);
-      const int site = r / 12, comp = r % 12;
-      if (site < nsite) {
-        const double2 t = terms[(((size_t)level * 12 + col) * V + y0) * 12 + r];
-        const int al = comp / 3, aa = comp % 3, be = col / 3, bb = col % 3;
-        double2& d = S[site][((al * 3 + aa) * 4 + be) * 3 + bb];
-        d.x += t.x;
-        d.y += t.y;
-        if (d.x != 0 || d.y != 0) nz[site] = 1;
+    bool any = false;
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) any = any || next[b][j].x != 0 || next[b][j].y != 0;
+    if (__ballot(any)) {   // (uniform over the wavefront; a term of zeros leaves S as it is)
+      live = true;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        double2 raw[3], v[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) raw[j] = make_double2(next[b][j].x, next[b][j].y);
+        quad_to_spin(k, raw, v);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) S[a][b] = cadd2(S[a][b], v[a]);
       }
     }
-    __syncthreads();
-    double2 acc = make_double2(0, 0);
-    if (ls < nsite && nz[ls])
-      for (int p = q; p < 36; p += kNucThreads) acc = cadd2(acc, nucleon_pair(S[ls], p));
-    part[tid] = acc;
-    __syncthreads();
-    if (q == 0 && ls < nsite) {
-      double2 s = part[tid];                    // fixed order over the site's threads
-      for (int k = 1; k < kNucThreads; ++k) s = cadd2(s, part[tid + k]);
-      if (PART) sites[ls] = s;
-      else W[(size_t)level * V + y0 + ls] = s;
-    }
-    if (PART) {
-      __syncthreads();
-      if (tid == 0) {
-        double2 s = sites[0];                   // fixed order over the workgroup's sites
-        for (int k = 1; k < nsite; ++k) s = cadd2(s, sites[k]);
-        W[(size_t)level * (V / kNucSites) + blockIdx.x] = s;
+    if (level + 1 < nlevels) load(level + 1);
+    double2 s = make_double2(0, 0);
+    if (live) {
+      s = nucleon_lane(S, lane);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        s.x += __shfl_xor(s.x, off, 64);
+        s.y += __shfl_xor(s.y, off, 64);
       }
     }
+    if (lane == 0) part[level & 1][w] = s;
     __syncthreads();
+    if (threadIdx.x == 0) P[(size_t)level * (V / kNucSites) + blockIdx.x] = cadd2(part[level & 1][0], part[level & 1][1]);
   }
 }
 
@@ -349,11 +408,10 @@ hipError_t launch_noise_trace(const double2* eta, const double2* phi, int nsrc, 
   return hipGetLastError();
 }
 
-hipError_t launch_nucleon(const double2* terms, size_t V, int T, int nlevels, double2* W, double2* out,
+hipError_t launch_nucleon(const double2* terms, size_t V, int T, int nlevels, double2* P, double2* out,
                           hipStream_t st) {
-  const unsigned blocks = (unsigned)((V + kNucSites - 1) / kNucSites);
-  hipLaunchKernelGGL(k_nucleon_site<false>, dim3(blocks), dim3(64), 0, st, terms, V, nlevels, W);
-  hipLaunchKernelGGL(k_slice_sum, dim3(T, nlevels), dim3(256), 0, st, W, V, T, out);
+  hipLaunchKernelGGL(k_nucleon, dim3((unsigned)(V / kNucSites)), dim3(128), 0, st, terms, V, nlevels, P);
+  hipLaunchKernelGGL(k_slice_sum, dim3(T, nlevels), dim3(256), 0, st, P, V / kNucSites, T, out);
   return hipGetLastError();
 }
 
@@ -402,15 +460,15 @@ hipError_t launch_nucleon_noalloc(const double2* terms, size_t V, int T, int nle
   if (device < 0 || device >= kMaxDevices || nlevels < 1 || T < 1 || V % ((size_t)T * kNucSites))
     return hipErrorInvalidValue;
   double2* P;
+  hipError_t e;
   {
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     P = g_scratch_ptr[device];
   }
   if (!P) return hipErrorNotInitialized;
   if ((size_t)nlevels * (V / kNucSites) * sizeof(double2) > kNucScratchBytes) return hipErrorInvalidValue;
-  const unsigned blocks = (unsigned)(V / kNucSites);
-  hipLaunchKernelGGL(k_nucleon_site<true>, dim3(blocks), dim3(64), 0, st, terms, V, nlevels, P);
-  hipLaunchKernelGGL(k_slice_sum, dim3(T, nlevels), dim3(256), 0, st, P, V / kNucSites, T, levels);
+  e = launch_nucleon(terms, V, T, nlevels, P, levels, st);
+  if (e != hipSuccess) return e;
   if (diffs) hipLaunchKernelGGL(k_level_diffs, dim3((T + 63) / 64), dim3(64), 0, st, levels, nlevels, T, diffs);
   return hipGetLastError();
 }

@@ -258,6 +258,42 @@ __device__ __forceinline__ void spinor_store_q(h16c* base, float* nrm, const flo
   stgf(nrm, m);
 }
 
+// ------------------------------------------- a canonical spinor in four lanes
+// Four lanes of a quad take one spin of a canonical spinor each.  Loaded as its
+// own three numbers a lane's 16-byte pieces lie 48 bytes from its neighbours',
+// and a wavefront load costs the texture addresser two to three times a
+// contiguous one's cycles; so the quad loads contiguous runs and sorts.
+template <int CTRL>
+__device__ __forceinline__ double2 quad_move(double2 v) {
+  const int a = __builtin_amdgcn_mov_dpp(__double2loint(v.x), CTRL, 0xf, 0xf, true);
+  const int b = __builtin_amdgcn_mov_dpp(__double2hiint(v.x), CTRL, 0xf, 0xf, true);
+  const int c = __builtin_amdgcn_mov_dpp(__double2loint(v.y), CTRL, 0xf, 0xf, true);
+  const int d = __builtin_amdgcn_mov_dpp(__double2hiint(v.y), CTRL, 0xf, 0xf, true);
+  return make_double2(__hiloint2double(b, a), __hiloint2double(d, c));
+}
+__device__ __forceinline__ double2 pick(bool c, double2 a, double2 b) {
+  return make_double2(c ? a.x : b.x, c ? a.y : b.y);
+}
+// A site's 12 numbers as lane q of the quad loads them, r[j] = number 4 j + q (64
+// contiguous bytes per load of the quad), become this lane's spin: v[a] = number
+// 3 q + a.  Number 3 q + a lies in lane (a - q) mod 4: every lane sends one.
+__device__ __forceinline__ void quad_to_spin(int q, const double2 r[3], double2 v[3]) {
+  v[0] = quad_move<0 | 3 << 2 | 2 << 4 | 1 << 6>(pick(q == 0 || q == 3, r[0], pick(q == 2, r[1], r[2])));
+  v[1] = quad_move<1 | 0 << 2 | 3 << 4 | 2 << 6>(pick(q == 1, r[0], pick(q == 2, r[2], r[1])));
+  v[2] = quad_move<2 | 1 << 2 | 0 << 4 | 3 << 6>(pick(q == 2, r[0], pick(q == 1, r[1], r[2])));
+}
+
+// and back: r[j] = number 4 j + q, which is entry (4 j + q) mod 3 of lane (4 j + q) / 3
+__device__ __forceinline__ void spin_to_quad(int q, const double2 v[3], double2 r[3]) {
+  // move v[a] to the lane that quad_to_spin took it from, then sort
+  const double2 t0 = quad_move<0 | 3 << 2 | 2 << 4 | 1 << 6>(v[0]);
+  const double2 t1 = quad_move<1 | 0 << 2 | 3 << 4 | 2 << 6>(v[1]);
+  const double2 t2 = quad_move<2 | 1 << 2 | 0 << 4 | 3 << 6>(v[2]);
+  r[0] = pick(q == 2, t2, pick(q == 1, t1, t0));
+  r[1] = pick(q == 1, t2, pick(q == 2, t0, t1));
+  r[2] = pick(q == 2, t1, pick(q == 1, t0, t2));
+}
+
 // local coordinates of EO index i of parity p
 __device__ __forceinline__ void eo_coords(const BoxGeom& g, int p, int i, int y[4]) {
   int j = i % g.half3;
