@@ -21,18 +21,19 @@ struct StreamJoin {
   Ctx* c;
   hipStream_t user;
   StreamJoin(Ctx* ctx, void* s) : c(ctx), user((hipStream_t)s) {
-    hipEvent_t e;
-    DDML_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    DDML_HIP(hipEventRecord(e, user));
-    DDML_HIP(hipStreamWaitEvent(c->stream, e, 0));
-    DDML_HIP(hipEventDestroy(e));
+    if (user == c->stream) return;   // a call inside a call
+    // every call behind a join uses buffers of the library's pool, which a
+    // captured graph would outlive
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    DDML_HIP(hipStreamIsCapturing(user, &cap));
+    if (cap != hipStreamCaptureStatusNone) throw Error{DDML_EDEVICE, "the caller's stream is being captured"};
+    DDML_HIP(hipEventRecord(c->join[0], user));
+    DDML_HIP(hipStreamWaitEvent(c->stream, c->join[0], 0));
   }
   void done() {
-    hipEvent_t e;
-    DDML_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    DDML_HIP(hipEventRecord(e, c->stream));
-    DDML_HIP(hipStreamWaitEvent(user, e, 0));
-    DDML_HIP(hipEventDestroy(e));
+    if (user == c->stream) return;
+    DDML_HIP(hipEventRecord(c->join[1], c->stream));
+    DDML_HIP(hipStreamWaitEvent(user, c->join[1], 0));
   }
 };
 

@@ -682,6 +682,271 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
   }
 }
 
+// ------------------------------------------------ D on canonical fields
+// out = D_Gamma in, both fields in the canonical layout of the host lattice,
+// out zero outside Gamma: one kernel from the caller's field to the caller's
+// field.  Four lanes per site, one per spin.  A quad of lanes loads and stores a
+// site's 192 contiguous bytes as three runs of 64 and sorts them into spins with
+// DPP moves.  The spin structure stays inside the quad as well:
+// ((1 -+ g_mu) psi)_s = psi_s -+ ph psi_{s'} with s' = s ^ 2 or 3 - s, and every lane
+// multiplies its own colour vector by the link, which is twice the SU(3) products
+// of the half-spinor form and no reconstruction.  A lane keeps R columns, so
+// that a link is read once for all of them.  Every workgroup also clears its
+// share of the rows outside Gamma: those stores wait for nothing.
+//
+// Bound by what the L2s fetch again: neighbour spinors and, once per group of
+// columns, links (32^3 x 16 of a 32^3 x 32 field, 12 columns: 11 GB of L2 misses
+// with R = 4 at 6.4 TB/s; 4.4 GB is what each input and output takes once).  So
+// more columns per lane are faster and more waves are not: 2.7 ms at R = 1 with
+// four waves per SIMD, 1.8 at R = 3, 1.65 at R = 4, 1.58 at R = 6, both with two.
+// The quadrant walk gives 1.72 against 2.03 ms for bands of time slices (R = 4),
+// streaming stores of rows that nothing reads again 1.53 against 1.59.  Measured
+// in all: 1.53 ms; 4.43 when the field was reordered to even-odd tiles and back
+// around two stencil launches (two gathers, two scatters and three fills, 1.75 ms
+// of it).  On 8 x 4^3 with one column 8 us instead of nine launches of 37.
+struct LexSite {
+  int y[4];
+  int s;        // lexicographic index in the box
+  size_t x;     // canonical site of the host lattice
+};
+__device__ __forceinline__ LexSite lex_site(const BoxGeom& g, const BlockSpec& bs, int s) {
+  LexSite l;
+  l.s = s;
+  int r = s;
+  l.y[3] = r % g.L[3]; r /= g.L[3];
+  l.y[2] = r % g.L[2]; r /= g.L[2];
+  l.y[1] = r % g.L[1];
+  l.y[0] = r / g.L[1];
+  l.x = (((size_t)(bs.lo[0] + l.y[0]) * bs.L[1] + bs.lo[1] + l.y[1]) * bs.L[2] + bs.lo[2] + l.y[2]) * bs.L[3] +
+        bs.lo[3] + l.y[3];
+  return l;
+}
+__device__ __forceinline__ int box_stride(const BoxGeom& g, int mu) {
+  return (mu < 3 ? g.L[3] : 1) * (mu < 2 ? g.L[2] : 1) * (mu < 1 ? g.L[1] : 1);
+}
+__device__ __forceinline__ long lat_stride(const BlockSpec& bs, int mu) {
+  return (long)(mu < 3 ? bs.L[3] : 1) * (mu < 2 ? bs.L[2] : 1) * (mu < 1 ? bs.L[1] : 1);
+}
+
+__device__ __forceinline__ double2 ldg2(const double2* p) {
+  const f64x2 u = *(const DDML_GLOBAL f64x2*)p;
+  return make_double2(u.x, u.y);
+}
+__device__ __forceinline__ void stg2nt(double2* p, double2 v) {
+  f64x2 u;
+  u.x = v.x; u.y = v.y;
+  __builtin_nontemporal_store(u, (DDML_GLOBAL f64x2*)p);
+}
+// the value of lane ^ 1, lane ^ 2 or lane ^ 3 of the quad
+template <int X>
+__device__ __forceinline__ double quad_xor(double v) {
+  constexpr int ctrl = X == 1 ? 0xB1 : (X == 2 ? 0x4E : 0x1B);
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+template <int X>
+__device__ __forceinline__ double2 quad_xor(double2 v) {
+  return make_double2(quad_xor<X>(v.x), quad_xor<X>(v.y));
+}
+
+// ((1 - d g_mu) psi)_s of this lane's spin: psi - d g_mu psi with
+//   (g_0 psi)_s = -psi_{s^2},              (g_2 psi)_s = -sg2 psi_{3-s}, sg2 = +, -, -, +
+//   (g_1 psi)_s = -i sg1 psi_{3-s}, sg1 = +, +, -, -,   (g_3 psi)_s = -i sg2 psi_{s^2}
+__device__ __forceinline__ double2 spin_term(int mu, bool fwd, double2 psi, double sg1, double sg2) {
+  const double2 o = (mu == 0 || mu == 3) ? quad_xor<2>(psi) : quad_xor<3>(psi);
+  const double d = fwd ? 1.0 : -1.0;
+  switch (mu) {
+    case 0: return fwd ? cadd(psi, o) : csub(psi, o);
+    case 1: return make_double2(fmadd(-d * sg1, o.y, psi.x), fmadd(d * sg1, o.x, psi.y));
+    case 2: return cmas(psi, o, d * sg2);
+    default: return make_double2(fmadd(-d * sg2, o.y, psi.x), fmadd(d * sg2, o.x, psi.y));
+  }
+}
+
+// R columns of one site (nr of them in use), this lane's spin
+template <int R>
+__device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, const LexSite& l, int spin,
+                                        const double2* __restrict__ U, const double2* __restrict__ A,
+                                        const double2* __restrict__ in, double2* __restrict__ out, size_t col, int nr) {
+  const int nt = g.ntiles, i = l.s >> 1;
+  const int par = (l.y[0] + l.y[1] + l.y[2] + l.y[3]) & 1;
+  const double sg1 = spin < 2 ? 1.0 : -1.0, sg2 = (spin == 0 || spin == 3) ? 1.0 : -1.0;
+  const double2* const mine = in + l.x * 12 + spin;   // lane q loads numbers q, q + 4, q + 8
+  // all eight hops, by a number that the compiler does not see: in one basic
+  // block it moves the loads of later hops up until registers spill
+  int hops;
+  asm volatile("s_movk_i32 %0, 0xff" : "=s"(hops));
+  double2 acc[R][3];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) acc[r][a] = make_double2(0, 0);
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      if (!((hops >> (2 * mu + dir)) & 1)) continue;
+      const bool fwd = dir == 0;
+      const int y = l.y[mu];
+      const int step = fwd ? (y + 1 == g.L[mu] ? 1 - g.L[mu] : 1) : (y == 0 ? g.L[mu] - 1 : -1);
+      const double2* src = mine + step * lat_stride(bs, mu) * 12;
+      double2 raw[R][3], w[3], u[9];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) raw[r][j] = ldg2(src + (r < nr ? r : 0) * col + 4 * j);
+      // the link the same way: lane q loads entries q, q + 4 and 8
+      const double2* ug = U + (fwd ? lidx(nt, par, mu, 0, i) : lidx(nt, 1 - par, mu, 0, (l.s + step * box_stride(g, mu)) >> 1));
+      const double2* uq = ug + 128 * (spin >> 1) + (spin & 1);
+      w[0] = ldg2(uq);
+      w[1] = ldg2(uq + 256);
+      w[2] = ldg2(ug + 512);
+#pragma unroll
+      for (int k = 0; k < 9; ++k)
+        u[k] = k == 8 ? w[2] : ((k & 3) == 0 ? quad_move<0x00>(w[k >> 2]) : ((k & 3) == 1 ? quad_move<0x55>(w[k >> 2]) :
+               ((k & 3) == 2 ? quad_move<0xAA>(w[k >> 2]) : quad_move<0xFF>(w[k >> 2]))));
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        double2 psi[3], h[3];
+        quad_to_spin(spin, raw[r], psi);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) h[a] = spin_term(mu, fwd, psi[a], sg1, sg2);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int b = 0; b < 3; ++b)
+            acc[r][a] = fwd ? cmac(acc[r][a], u[3 * a + b], h[b]) : cmacc(acc[r][a], u[3 * b + a], h[b]);
+      }
+    }
+  // (A psi)_s: this spin's three rows of its chiral 6x6 block.  Spin 0 of the
+  // block (rows 0..2) takes the cross entries as they are stored, spin 1 their
+  // adjoint.
+  const int blk = spin >> 1;
+  const bool low = spin & 1;
+  const double2* cl = A + cidx(nt, par, 18 * blk, i);
+  auto slot = [&](int k) { return ldg2(cl + 128 * (k >> 1) + (k & 1)); };
+  auto up = [](int r, int c) { return 3 + r * (11 - r) / 2 + (c - r - 1); };
+  const double2 d0 = slot(0), d1 = slot(1), d2 = slot(2);
+  const double dg[3] = {low ? d1.y : d0.x, low ? d2.x : d0.y, low ? d2.y : d1.x};
+  const double2 o01 = slot(low ? up(3, 4) : up(0, 1)), o02 = slot(low ? up(3, 5) : up(0, 2)),
+                o12 = slot(low ? up(4, 5) : up(1, 2));
+  double2 x[3][3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) x[a][b] = slot(up(a, 3 + b));
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = a; b < 3; ++b) {
+      const double2 p = x[a][b], q = x[b][a];
+      x[a][b] = make_double2(low ? q.x : p.x, low ? -q.y : p.y);
+      if (b > a) x[b][a] = make_double2(low ? p.x : q.x, low ? -p.y : q.y);
+    }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    double2 raw[3], v[3], w[3], q[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) raw[j] = ldg2(mine + (r < nr ? r : 0) * col + 4 * j);
+    quad_to_spin(spin, raw, v);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) w[a] = quad_xor<1>(v[a]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) q[a] = cscale(v[a], dg[a]);
+    q[0] = cmac(cmac(q[0], o01, v[1]), o02, v[2]);
+    q[1] = cmac(cmacc(q[1], o01, v[0]), o12, v[2]);
+    q[2] = cmacc(cmacc(q[2], o02, v[0]), o12, v[1]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) q[a] = cmac(q[a], x[a][b], w[b]);
+      q[a] = cscale(cmas(q[a], acc[r][a], -bs.kappa), 1.0 / (2.0 * bs.kappa));
+    }
+    if (r < nr) {
+      double2* o = out + l.x * 12 + spin + r * col;
+      double2 t[3];
+      spin_to_quad(spin, q, t);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) stg2nt(o + 4 * j, t[j]);
+    }
+  }
+}
+
+// Clears the part outside Gamma of rows [r0, r1) of the field's nrhs L0 L1 L2
+// rows of L3 sites, one wave per row.
+__device__ __forceinline__ void clear_rows(const BoxGeom& g, const BlockSpec& bs, double2* __restrict__ out, long r0,
+                                           long r1) {
+  const int lane = threadIdx.x & 63;
+  for (long r = r0 + (threadIdx.x >> 6); r < r1; r += blockDim.x >> 6) {
+    long q = r;
+    const int x2 = (int)(q % bs.L[2]) - bs.lo[2]; q /= bs.L[2];
+    const int x1 = (int)(q % bs.L[1]) - bs.lo[1]; q /= bs.L[1];
+    const int x0 = (int)(q % bs.L[0]) - bs.lo[0];
+    const bool crosses = (unsigned)x0 < (unsigned)g.L[0] && (unsigned)x1 < (unsigned)g.L[1] &&
+                         (unsigned)x2 < (unsigned)g.L[2];
+    if (crosses && g.L[3] == bs.L[3]) continue;
+    const int a = crosses ? 12 * bs.lo[3] : 0, skip = crosses ? 12 * g.L[3] : 0;   // the row's part inside Gamma
+    double2* row = out + (size_t)r * bs.L[3] * 12;
+    for (int k = lane; k < 12 * bs.L[3] - skip; k += 64) stg2nt(row + (k < a ? k : k + skip), make_double2(0, 0));
+  }
+}
+
+// A workgroup is R columns of 64 sites of the box in lexicographic order (one
+// tile, 16 sites per wavefront); the groups of columns of a tile follow each
+// other on its XCD.
+struct DwWalk {
+  const int* tile;       // XCD x works through tile[xoff[x] .. xoff[x+1])
+  int xoff[kXcd + 1];
+};
+template <int R>
+__global__ void __launch_bounds__(256, 2)
+    k_apply_d(BoxGeom g, BlockSpec bs, DwWalk walk, const double2* __restrict__ U, const double2* __restrict__ A,
+              const double2* __restrict__ in, double2* __restrict__ out, int nrhs, int ntl, long rows) {
+  const size_t col = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * bs.L[3] * 12;
+  const int x = blockIdx.x % kXcd, nb = gridDim.x / kXcd;
+  const int* tiles = walk.tile + walk.xoff[x];
+  const int ng = (nrhs + R - 1) / R, n = (walk.xoff[x + 1] - walk.xoff[x]) * ng;
+  for (int v = blockIdx.x / kXcd; v < n; v += nb) {
+    const int tile = ldg(tiles + v / ng), c = (v % ng) * R;
+    if (rows && c == 0) clear_rows(g, bs, out, tile * rows / ntl, (tile + 1) * rows / ntl);
+    const int s = tile * kTile + (threadIdx.x >> 2);
+    if (s >= 2 * g.Vh) continue;   // (the four lanes of a site together)
+    dw_site<R>(g, bs, lex_site(g, bs, s), threadIdx.x & 3, U, A, in + c * col, out + c * col, col, min(R, nrhs - c));
+  }
+}
+
+hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk, const int* xoff, const double2* U,
+                          const double2* A, const double2* in, double2* out, int nrhs, hipStream_t st) {
+  if (nrhs < 1 || nrhs > kMaxRhs) return hipErrorInvalidValue;
+  DwWalk w{walk, {}};
+  for (int x = 0; x <= kXcd; ++x) w.xoff[x] = xoff[x];
+  const int ntl = xoff[kXcd];
+  bool all = true;
+  for (int m = 0; m < 4; ++m) all = all && g.L[m] == bs.L[m];
+  const long rows = all ? 0 : (long)nrhs * bs.L[0] * bs.L[1] * bs.L[2];
+  // groups of six columns at most (what two waves per SIMD have registers for),
+  // as even as they come
+  const int groups = (nrhs + 5) / 6;
+  int grid = ntl * groups < 16384 ? ntl * groups : 16384;
+  grid = (grid + kXcd - 1) / kXcd * kXcd;
+#define DDML_DW(Rv)                                                                                                 \
+  case Rv:                                                                                                          \
+    hipLaunchKernelGGL(k_apply_d<Rv>, dim3(grid), dim3(256), 0, st, g, bs, w, U, A, in, out, nrhs, ntl, rows);      \
+    break;
+  switch ((nrhs + groups - 1) / groups) {
+    DDML_DW(1)
+    DDML_DW(2)
+    DDML_DW(3)
+    DDML_DW(4)
+    DDML_DW(5)
+    DDML_DW(6)
+    default: return hipErrorInvalidValue;
+  }
+#undef DDML_DW
+  return hipGetLastError();
+}
+
 // Batched launch over solver slots.  Linear order: virtual tile vt of the
 // batch maps to (slot, tile) through tile_start[nslots+1].  Other orders:
 // XCD x walks xstart[x][*], the prefix over slots of its share of the tiles.
@@ -799,7 +1064,6 @@ static hipError_t hop_item_impl(const HopItem<T2>& it, int mode, int red, int R,
   if (order != TILE_ORDER_LINEAR) grid = ((grid + kXcd - 1) / kXcd) * kXcd;
   DDML_HOP_DISPATCH(T2, 1, MODE_CINV_HOP, RED_NONE)
   DDML_HOP_DISPATCH(T2, 1, MODE_SCHUR, RED_NONE)
-  DDML_HOP_DISPATCH(T2, 1, MODE_M, RED_NONE)
   DDML_HOP_DISPATCH(T2, 1, MODE_PREP, RED_NONE)
   DDML_HOP_DISPATCH(T2, 1, MODE_RES, RED_NORM)
   DDML_HOP_DISPATCH(T2, 2, MODE_CINV_HOP, RED_NONE)

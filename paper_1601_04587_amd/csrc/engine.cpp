@@ -97,9 +97,12 @@ Ctx::~Ctx() {
   run64.clear();
   run16.clear();
   blocks.clear();
+  walks.clear();
   gauges.clear();
   flag.reset();
   if (pinned) (void)hipHostFree(pinned);
+  for (hipEvent_t e : join)
+    if (e) (void)hipEventDestroy(e);
   pool.reset();
   if (stream) (void)hipStreamDestroy(stream);
 }
@@ -133,6 +136,7 @@ void ctx_init(Ctx* c, const ddml_lattice* lat, int device, size_t budget) {
   c->V = (size_t)lat->dims[0] * lat->dims[1] * lat->dims[2] * lat->dims[3];
   if (c->V > (size_t)1 << 30) throw Error{DDML_EINVAL, "lattice too large"};
   DDML_HIP(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
+  for (hipEvent_t& e : c->join) DDML_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   if (budget == 0) {
     size_t fr = 0, tot = 0;
     DDML_HIP(hipMemGetInfo(&fr, &tot));
@@ -353,13 +357,48 @@ static void build_walk(const BoxGeom& g, int tps, int nrg, int nsub, bool split_
     throw Error{DDML_EDEVICE, "internal: tile walk is not a permutation"};
 }
 
+// The walks of a box: they depend on its extents alone, so every gauge version
+// and every domain of the same extents shares them (building and uploading them
+// again cost 0.1 ms of each new version's operator).  A context that has seen
+// kMaxWalks shapes starts over; blocks keep the walks they hold.
+constexpr size_t kMaxWalks = 64;
+static std::shared_ptr<WalkSet> walks_of(Ctx* c, const BoxGeom& g, int tps) {
+  const std::array<int, 4> key{g.L[0], g.L[1], g.L[2], g.L[3]};
+  auto it = c->walks.find(key);
+  if (it != c->walks.end()) return it->second;
+  auto ws = std::make_shared<WalkSet>();
+  std::vector<int> all, one;
+  for (int w = 0; w < kWalks; ++w) {
+    // orders 2, 3, 4: x1 ranges split into 2 / 4 / 4 sub-bands along x2 (order 4
+    // in blocks of 4 slices); order 5: regions of half the x1 rows and a quarter
+    // of the tiles of a plane, 4 sub-bands along x1, blocks of 4 slices
+    if (w < 3) build_walk(g, tps, 1, w == 0 ? 2 : 4, false, w == 2 ? 4 : 1, one, ws->xoff[w]);
+    else build_walk(g, tps, 4, 4, true, 4, one, ws->xoff[w]);
+    all.insert(all.end(), one.begin(), one.end());
+  }
+  // apply_D's tiles are 64 sites of both parities, 32 of each
+  const int lex = (g.Vh + kTile / 2 - 1) / (kTile / 2);
+  const long slice = (long)g.L[1] * g.L[2] * g.L[3];
+  if (!tile_walk(g.L, lex, slice % kTile == 0 ? (int)(slice / kTile) : 0, kTile / 2, kXcd, 4, 4, true, 4, one,
+                 ws->xlex))
+    throw Error{DDML_EDEVICE, "internal: tile walk is not a permutation"};
+  ws->lex = all.size();
+  all.insert(all.end(), one.begin(), one.end());
+  ws->walk = DBuf(c->pool.get(), sizeof(int) * all.size());
+  DDML_HIP(hipMemcpyAsync(ws->walk.p, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice, c->stream));
+  DDML_HIP(hipStreamSynchronize(c->stream));   // `all` goes away
+  if (c->walks.size() >= kMaxWalks) c->walks.clear();
+  c->walks[key] = ws;
+  return ws;
+}
+
 // Attaches the walk of `order` (if it uses one) to a kernel argument.
 template <typename D>
 static void attach_walk(D& d, const OpBlock& ob, int order) {
   if (order >= TILE_ORDER_SUB2) {
     const int w = order - TILE_ORDER_SUB2;
-    d.walk = ob.walk[w].as<int>();
-    for (int x = 0; x <= kXcd; ++x) d.xoff[x] = ob.xoff[w][x];
+    d.walk = ob.walks->walk.as<int>() + (size_t)w * ob.ntiles;
+    for (int x = 0; x <= kXcd; ++x) d.xoff[x] = ob.walks->xoff[w][x];
   } else {
     d.walk = nullptr;
   }
@@ -394,17 +433,7 @@ std::shared_ptr<OpBlock> opblock(Ctx* c, int gauge_id, int dom_id) {
   ob->Ainv32 = DBuf(c->pool.get(), kCloverSlots * ns * sizeof(float2));
   for (DBuf* b : {&ob->U64, &ob->U32, &ob->A64, &ob->Ainv64, &ob->Ainv32})
     DDML_HIP(hipMemsetAsync(b->p, 0, b->bytes, c->stream));
-  std::vector<int> walks[kWalks];
-  for (int w = 0; w < kWalks; ++w) {
-    // orders 2, 3, 4: x1 ranges split into 2 / 4 / 4 sub-bands along x2 (order 4
-    // in blocks of 4 slices); order 5: regions of half the x1 rows and a quarter
-    // of the tiles of a plane, 4 sub-bands along x1, blocks of 4 slices
-    if (w < 3) build_walk(ob->g, ob->tps, 1, w == 0 ? 2 : 4, false, w == 2 ? 4 : 1, walks[w], ob->xoff[w]);
-    else build_walk(ob->g, ob->tps, 4, 4, true, 4, walks[w], ob->xoff[w]);
-    ob->walk[w] = DBuf(c->pool.get(), sizeof(int) * walks[w].size());
-    DDML_HIP(hipMemcpyAsync(ob->walk[w].p, walks[w].data(), sizeof(int) * walks[w].size(), hipMemcpyHostToDevice,
-                            c->stream));
-  }
+  ob->walks = walks_of(c, ob->g, ob->tps);
   GaugeView gv;
   gv.base = git->second.base->as<double2>();
   gv.region = git->second.region ? git->second.region->as<double2>() : nullptr;
@@ -496,31 +525,20 @@ static HopItem<double2> item64(const OpBlock& ob, int nrhs, int order) {
 
 void apply_D(Ctx* c, int gauge_id, int dom_id, const double* in, double* out, int nrhs, hipStream_t st) {
   auto ob = opblock(c, gauge_id, dom_id);
-  const size_t n = (size_t)nrhs * ob->field;
-  DBuf xe(c->pool.get(), n * sizeof(double2)), xo(c->pool.get(), n * sizeof(double2));
-  DBuf oe(c->pool.get(), n * sizeof(double2)), oo(c->pool.get(), n * sizeof(double2));
-  DDML_HIP(hipMemsetAsync(xe.p, 0, xe.bytes, st));
-  DDML_HIP(hipMemsetAsync(xo.p, 0, xo.bytes, st));
-  const double2* cin = reinterpret_cast<const double2*>(in);
-  double2* cout = reinterpret_cast<double2*>(out);
-  DDML_HIP(launch_gather(cin, ob->bs, 0, nrhs, 1.0, xe.as<double2>(), st));
-  DDML_HIP(launch_gather(cin, ob->bs, 1, nrhs, 1.0, xo.as<double2>(), st));
-  const double kappa = ob->bs.kappa;
-  for (int p = 0; p < 2; ++p) {
-    HopItem<double2> it = item64(*ob, nrhs, c->tune64.order);
-    it.clov = ob->A64.as<double2>();
-    it.in = p == 0 ? xo.as<double2>() : xe.as<double2>();
-    it.aux = p == 0 ? xe.as<double2>() : xo.as<double2>();
-    it.out = p == 0 ? oe.as<double2>() : oo.as<double2>();
-    it.par_out = p;
-    it.c1 = kappa;
-    it.c2 = 1.0 / (2.0 * kappa);
-    DDML_HIP(launch_hop_item(it, MODE_M, RED_NONE, 1, c->tune64.order, st));
+  const size_t bytes = (size_t)nrhs * gauge_get(c, gauge_id).V * 12 * sizeof(double2);
+  const char* a = reinterpret_cast<const char*>(in);
+  const char* b = reinterpret_cast<const char*>(out);
+  DBuf copy;   // of an input that the output overwrites
+  if (a < b + bytes && b < a + bytes) {
+    copy = DBuf(c->pool.get(), bytes);
+    DDML_HIP(hipMemcpyAsync(copy.p, in, bytes, hipMemcpyDeviceToDevice, st));
+    in = copy.as<double>();
   }
-  DDML_HIP(hipMemsetAsync(out, 0, (size_t)nrhs * gauge_get(c, gauge_id).V * 12 * sizeof(double2), st));
-  DDML_HIP(launch_scatter(oe.as<double2>(), ob->bs, 0, nrhs, 1.0, cout, st));
-  DDML_HIP(launch_scatter(oo.as<double2>(), ob->bs, 1, nrhs, 1.0, cout, st));
-  DDML_HIP(hipStreamSynchronize(st));  // temporaries go back to the pool
+  // (the operator data and the copy may go back to the pool before the kernel
+  // has run: every later use of the pool's memory is on the same stream)
+  const WalkSet& ws = *ob->walks;
+  DDML_HIP(launch_apply_d(ob->g, ob->bs, ws.walk.as<int>() + ws.lex, ws.xlex, ob->U64.as<double2>(), ob->A64.as<double2>(),
+                          reinterpret_cast<const double2*>(in), reinterpret_cast<double2*>(out), nrhs, st));
 }
 
 // Couplings of D from outside a domain into it; no operator block is needed:

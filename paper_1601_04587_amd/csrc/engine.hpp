@@ -7,6 +7,7 @@
 #include <condition_variable>
 #include <cstdint>
 #include <deque>
+#include <array>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -94,6 +95,15 @@ struct DomainRec {
   int lo[4], hi[4];
 };
 
+// Tile walks of one box: TILE_ORDER_SUB2, SUB4, SUB4T and QUAD one after the
+// other, then from entry `lex` on the quadrant walk of its lexicographic tiles.
+struct WalkSet {
+  DBuf walk;
+  int xoff[kWalks][kXcd + 1] = {};
+  size_t lex = 0;
+  int xlex[kXcd + 1] = {};
+};
+
 struct OpBlock {
   BlockSpec bs;
   BoxGeom g;
@@ -103,8 +113,7 @@ struct OpBlock {
   DBuf U64, A64, Ainv64;   // FP64 operator data
   DBuf U32, Ainv32;        // FP32 copies for the inner solve
   DBuf U16, Ainv16, Ainv16n;  // 16-bit copies (built on first use by a DDML_MIXED_FP16 solve)
-  DBuf walk[kWalks];       // tile walks of TILE_ORDER_SUB2, SUB4, SUB4T, QUAD
-  int xoff[kWalks][kXcd + 1] = {};
+  std::shared_ptr<WalkSet> walks;
   size_t bytes = 0;
   bool su3 = true;         // links are SU(3) to 1e-5 (the FP32 and 16-bit copies keep two rows)
 };
@@ -219,6 +228,7 @@ struct Ctx {
   int device = 0;
   size_t V = 0;
   hipStream_t stream = nullptr;
+  hipEvent_t join[2] = {nullptr, nullptr};   // order a caller's stream and `stream` (under mu)
   std::unique_ptr<DevPool> pool;
   std::recursive_mutex mu;
   std::atomic<int> api_waiting{0};   // API calls waiting for mu (the request loop yields to them)
@@ -227,6 +237,7 @@ struct Ctx {
   std::map<int, GaugeRec> gauges;
   std::map<int, DomainRec> domains;
   std::map<std::pair<int, int>, std::shared_ptr<OpBlock>> blocks;
+  std::map<std::array<int, 4>, std::shared_ptr<WalkSet>> walks;   // by box extents
   std::map<int, std::unique_ptr<BatchRunner<float2>>> run32;   // by nrhs
   std::map<int, std::unique_ptr<BatchRunner<double2>>> run64;
   std::map<int, std::unique_ptr<BatchRunner<h16c>>> run16;

@@ -4,6 +4,15 @@
 
 namespace ddml {
 
+// One domain on the lattice of its gauge field.
+struct BlockSpec {
+  int L[4];       // lattice
+  int lo[4];      // domain origin
+  int Lb[4];      // domain extents (even)
+  int tbc;        // time boundary of the lattice: 0 periodic, 1 antiperiodic, 2 open
+  double kappa, csw;
+};
+
 // dirac.hip
 hipError_t launch_hop_item(const HopItem<double2>& it, int mode, int red, int R, int order, hipStream_t st);
 // xstart: [kXcd][xstride] per-XCD prefix of tile counts (all orders but linear);
@@ -25,6 +34,11 @@ inline int band_count(int ntiles, int tps, int x) {
   const int lo = (int)((long)x * S / kXcd), hi = (int)((long)(x + 1) * S / kXcd);
   return (hi - lo) * (ntiles / S);
 }
+// out = D_Gamma in on canonical [nrhs][V][12] fields (not overlapping), zero
+// outside Gamma = [bs.lo, bs.lo + bs.Lb); U, A the FP64 links and clover term
+// (walk, xoff: the box's lexicographic 64-site tiles by XCD)
+hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk, const int* xoff, const double2* U,
+                          const double2* A, const double2* in, double2* out, int nrhs, hipStream_t st);
 hipError_t launch_clover_apply(const BoxGeom& g, const double2* clov, int p, const double2* in, double2* out,
                                int nrhs, hipStream_t st);
 
@@ -98,13 +112,6 @@ struct GaugeView {
   const double2* base;    // [V][4][9] canonical FP64 links of the whole lattice
   const double2* region;  // [V_region][4][9] override for time slices [r_t0, r_t1), may be null
   int r_t0, r_t1;
-};
-struct BlockSpec {
-  int L[4];       // lattice
-  int lo[4];      // domain origin
-  int Lb[4];      // domain extents (even)
-  int tbc;        // time boundary of the lattice: 0 periodic, 1 antiperiodic, 2 open
-  double kappa, csw;
 };
 // FP64 links (5-pair layout) and the two-row FP32 copy; bit 2 of *bad if a link is not SU(3)
 hipError_t launch_build_links(const GaugeView& gv, const BlockSpec& bs, double2* U64, float2* U32, int* bad,
