@@ -240,22 +240,45 @@ int gauge_region(Ctx* c, int base, int t0, int t1, const double* U, int on_devic
   return id;
 }
 
+// A temporary of the pool, or an empty buffer where it does not fit.
+static DBuf scratch(Ctx* c, size_t bytes) {
+  try {
+    return DBuf(c->pool.get(), bytes);
+  } catch (const Error& e) {
+    if (e.code != DDML_ENOMEM) throw;
+    return DBuf();
+  }
+}
+
 int gauge_level1(Ctx* c, int base, int t0, int t1, double beta, uint64_t seed, uint32_t stream, int nsweeps,
                  int n_or) {
   if (!(beta > 0) || nsweeps < 0 || n_or < 0) throw Error{DDML_EINVAL, "need beta > 0, nsweeps >= 0, n_or >= 0"};
   const GaugeRec* overlay;
   GaugeRec g = version_of(c, base, t0, t1, &overlay);
   const size_t V3 = g.V / g.lat.dims[0], link = 36 * sizeof(double2);
-  // the region starts from the parent's links on [t0, t1)
-  DDML_HIP(hipMemcpyAsync(g.region->p, g.base->as<double2>() + (size_t)t0 * V3 * 36, g.region->bytes,
-                          hipMemcpyDeviceToDevice, c->stream));
-  if (overlay)
-    DDML_HIP(hipMemcpyAsync((char*)g.region->p + (size_t)(overlay->r_t0 - t0) * V3 * link, overlay->region->p,
-                            (size_t)(overlay->r_t1 - overlay->r_t0) * V3 * link, hipMemcpyDeviceToDevice, c->stream));
-  const GaugeView gv{g.base->as<double2>(), g.region->as<double2>(), t0, t1};
   BlockSpec bs{};
   for (int m = 0; m < 4; ++m) bs.L[m] = g.lat.dims[m];
-  DDML_HIP(launch_level1_sweeps(gv, g.region->as<double2>(), bs, beta, seed, stream, nsweeps, n_or, c->stream));
+  BoxLinks copy = level1_box(bs, t0, t1);
+  DBuf work;
+  const size_t cb = DevPool::round(box_links_bytes(copy));
+  if (nsweeps > 0) work = scratch(c, cb + level1_staple_bytes(bs, t0, t1));   // without it: swept in place below
+  if (work.p) {
+    copy.W = work.as<double2>();
+    const GaugeView parent{g.base->as<double2>(), overlay ? overlay->region->as<double2>() : nullptr,
+                           overlay ? overlay->r_t0 : 0, overlay ? overlay->r_t1 : 0};
+    DDML_HIP(launch_level1_slab(parent, g.region->as<double2>(), copy, reinterpret_cast<double2*>((char*)work.p + cb), bs,
+                                t0, t1, beta, seed, stream, nsweeps, n_or, c->stream));
+  } else {
+    // the region starts from the parent's links on [t0, t1)
+    DDML_HIP(hipMemcpyAsync(g.region->p, g.base->as<double2>() + (size_t)t0 * V3 * 36, g.region->bytes,
+                            hipMemcpyDeviceToDevice, c->stream));
+    if (overlay)
+      DDML_HIP(hipMemcpyAsync((char*)g.region->p + (size_t)(overlay->r_t0 - t0) * V3 * link, overlay->region->p,
+                              (size_t)(overlay->r_t1 - overlay->r_t0) * V3 * link, hipMemcpyDeviceToDevice,
+                              c->stream));
+    const GaugeView gv{g.base->as<double2>(), g.region->as<double2>(), t0, t1};
+    DDML_HIP(launch_level1_sweeps(gv, bs, beta, seed, stream, nsweeps, n_or, c->stream));
+  }
   DDML_HIP(hipStreamSynchronize(c->stream));
   const int id = c->next_gauge++;
   c->gauges[id] = std::move(g);
@@ -266,10 +289,15 @@ void gauge_copy_out(Ctx* c, int id, double* U, int on_device) {
   const GaugeRec& g = gauge_get(c, id);
   const size_t V3 = g.V / g.lat.dims[0], link = 36 * sizeof(double2);
   const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  DDML_HIP(hipMemcpyAsync(U, g.base->p, g.V * link, kind, c->stream));
-  if (g.region)
-    DDML_HIP(hipMemcpyAsync((char*)U + (size_t)g.r_t0 * V3 * link, g.region->p,
-                            (size_t)(g.r_t1 - g.r_t0) * V3 * link, kind, c->stream));
+  // slices [a, b) of the field from `src`
+  auto slices = [&](int a, int b, const void* src) {
+    if (b > a)
+      DDML_HIP(hipMemcpyAsync((char*)U + (size_t)a * V3 * link, src, (size_t)(b - a) * V3 * link, kind, c->stream));
+  };
+  const int T = g.lat.dims[0], a = g.region ? g.r_t0 : T, b = g.region ? g.r_t1 : T;
+  slices(0, a, g.base->p);
+  if (g.region) slices(a, b, g.region->p);
+  slices(b, T, (const char*)g.base->p + (size_t)b * V3 * link);
   DDML_HIP(hipStreamSynchronize(c->stream));
 }
 

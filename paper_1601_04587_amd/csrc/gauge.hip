@@ -13,6 +13,8 @@
 // factorisation (a non-positive pivot is reported).  The clover term of every
 // site of the domain is built from the full gauge field, so D_Gamma is exactly
 // the diagonal block of D (eq. blkdec).
+#include <type_traits>
+
 #include "ddml_common.hpp"
 #include "launchers.hpp"
 
@@ -48,6 +50,136 @@ __device__ __forceinline__ void lex_coords(const int Lb[4], int s, int y[4]) {
 __host__ __device__ __forceinline__ int ntiles_of(const BlockSpec& bs) {
   const int Vh = bs.Lb[0] * bs.Lb[1] * bs.Lb[2] * bs.Lb[3] / 2;
   return (Vh + kTile - 1) / kTile;
+}
+
+// Where a kernel finds the links around the sites it works on.  In a working
+// copy (launch_box_links) entry e of a link lies 64 e complex numbers from its
+// first, the 64 sites of a parity's tile side by side, so that a wavefront reads
+// an entry as one contiguous run; in the canonical links, read when the copy
+// does not fit, every lane reads cache lines of its own.
+__device__ __forceinline__ double2* BoxLinks::at(const int L[4], const int x[4], int mu) const {
+  int y[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    y[m] = x[m] - o[m];
+    y[m] = y[m] < 0 ? y[m] + L[m] : y[m];
+  }
+  const int lex = ((y[0] * E[1] + y[1]) * E[2] + y[2]) * E[3] + y[3];
+  const int par = (y[0] + y[1] + y[2] + y[3]) & 1, i = lex >> 1;
+  return W + (((size_t)(mu * 2 + par) * nt + (i >> 6)) * 9) * 64 + (i & 63);
+}
+// Block b of n in the order in which XCD b mod 8 works through one contiguous
+// eighth: neighbours in the lattice then share an L2.
+__device__ __forceinline__ int xcd_chunk(int b, int n) {
+  const int x = b % kXcd, q = n / kXcd, r = n % kXcd;   // the first r XCDs have one block more
+  return x * q + (x < r ? x : r) + b / kXcd;
+}
+struct CanonLinks {
+  GaugeView gv;
+  static constexpr int kStep = 1;
+  __device__ __forceinline__ double2* at(const int L[4], const int x[4], int mu) const {
+    return const_cast<double2*>(link_ptr(gv, L, x, mu));
+  }
+};
+
+// Canonical links of a box (lattice-periodic) <-> its working copy: 64 sites per
+// workgroup through LDS, both sides in contiguous runs.  Writing back (IN =
+// false) goes to the slices of a region that starts with the box.
+constexpr int kCopyPitch = 37;   // 36 complex per site and one pad (bank conflicts)
+template <bool IN>
+__global__ void __launch_bounds__(256) k_box_copy(GaugeView gv, double2* __restrict__ region, BlockSpec bs,
+                                                   BoxLinks bl, int nsites) {
+  __shared__ double2 sm[64 * kCopyPitch];
+  const int s0 = blockIdx.x * 64, ns = min(64, nsites - s0);
+  auto coords = [&](int lex, int y[4]) {
+    y[3] = lex % bl.E[3]; lex /= bl.E[3];
+    y[2] = lex % bl.E[2]; lex /= bl.E[2];
+    y[1] = lex % bl.E[1];
+    y[0] = lex / bl.E[1];
+  };
+  auto pack = [&](int q, int& lds, double2*& w) {   // q: entry of the tile, sites of a parity fastest
+    const int e = q >> 6, p = (q >> 5) & 1, j = q & 31;
+    if (2 * j >= ns) return false;
+    int y[4];
+    coords(s0 + 2 * j, y);
+    const int odd = (p + y[0] + y[1] + y[2]) & 1;   // the pair's site of parity p
+    lds = (2 * j + odd) * kCopyPitch + e;
+    const int mu = e / 9, i = (s0 >> 1) + j;
+    w = bl.W + (((size_t)(mu * 2 + p) * bl.nt + (i >> 6)) * 9 + (e - 9 * mu)) * 64 + (i & 63);
+    return true;
+  };
+  auto canon = [&](int q, int& lds) {   // q: entry of the tile, entries of a site fastest
+    const int site = q / 36, e = q - 36 * site;
+    lds = site * kCopyPitch + e;
+    if (!IN) return region + ((size_t)(s0 + site) * 36 + e);
+    int x[4];
+    coords(s0 + site, x);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      x[m] += bl.o[m];
+      x[m] = x[m] >= bs.L[m] ? x[m] - bs.L[m] : x[m];
+    }
+    return const_cast<double2*>(link_ptr(gv, bs.L, x, 0) + e);
+  };
+  if (IN) {
+    for (int q = threadIdx.x; q < 36 * ns; q += 256) {
+      int lds;
+      const double2* src = canon(q, lds);
+      sm[lds] = *src;
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 36 * 64; q += 256) {
+      int lds;
+      double2* w;
+      if (pack(q, lds, w)) *w = sm[lds];
+    }
+  } else {
+    for (int q = threadIdx.x; q < 36 * 64; q += 256) {
+      int lds;
+      double2* w;
+      if (pack(q, lds, w)) sm[lds] = *w;
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 36 * ns; q += 256) {
+      int lds;
+      double2* dst = canon(q, lds);
+      *dst = sm[lds];
+    }
+  }
+}
+
+static int sites_of(const BoxLinks& bl) { return bl.E[0] * bl.E[1] * bl.E[2] * bl.E[3]; }
+
+size_t box_links_bytes(const BoxLinks& bl) { return (size_t)8 * bl.nt * 9 * 64 * sizeof(double2); }
+
+static void set_box(BoxLinks& bl) { bl.nt = (sites_of(bl) / 2 + 63) / 64; }
+
+BoxLinks clover_box(const BlockSpec& bs) {
+  BoxLinks bl{};
+  for (int m = 0; m < 4; ++m) {
+    const bool cut = bs.Lb[m] != bs.L[m];
+    bl.o[m] = cut ? (bs.lo[m] + bs.L[m] - 1) % bs.L[m] : 0;
+    bl.E[m] = cut ? bs.Lb[m] + 2 : bs.L[m];
+  }
+  set_box(bl);
+  return bl;
+}
+
+BoxLinks level1_box(const BlockSpec& bs, int t0, int t1) {
+  BoxLinks bl{};
+  for (int m = 0; m < 4; ++m) bl.E[m] = bs.L[m];
+  if (t1 - t0 < bs.L[0]) {
+    bl.o[0] = t0;
+    bl.E[0] = t1 - t0 + 1;
+  }
+  set_box(bl);
+  return bl;
+}
+
+hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const BlockSpec& bs, hipStream_t st) {
+  const int n = sites_of(bl);
+  hipLaunchKernelGGL(k_box_copy<true>, dim3((n + 63) / 64), dim3(256), 0, st, gv, nullptr, bs, bl, n);
+  return hipGetLastError();
 }
 
 // FP64 links in the 5-pair layout; the FP32 copy keeps the first two rows
@@ -557,8 +689,8 @@ hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const doubl
 __device__ __forceinline__ void philox4x32_10(uint32_t x[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(0xD2511F53u, x[0]), lo0 = 0xD2511F53u * x[0];
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, x[2]), lo1 = 0xCD9E8D57u * x[2];
+    const uint64_t p0 = (uint64_t)0xD2511F53u * x[0], p1 = (uint64_t)0xCD9E8D57u * x[2];
+    const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0, hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
     const uint32_t y0 = hi1 ^ x[1] ^ k0, y2 = hi0 ^ x[3] ^ k1;
     x[0] = y0;
     x[1] = lo1;
@@ -590,33 +722,57 @@ struct LinkDraws {
   }
 };
 
-// A = sum over nu != mu of U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag + U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-__device__ void wilson_staples(const GaugeView& gv, const int L[4], const int x[4], int mu, double2 A[9]) {
+// A += sign times one staple of U_mu(x) in the (mu, nu) plane:
+//   up    U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
+//   down  U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
+// row by row, so that two of its three links and A are live.
+template <typename Links>
+__device__ __forceinline__ void add_staple(const Links& links, const int L[4], const int x[4], int mu, int nu,
+                                           bool down, double sign, double2 A[9]) {
+  constexpr int S = Links::kStep;
+  int y[4];
+  nbr(L, x, mu, 1, nu, down ? -1 : 0, y);
+  const double2* pa = links.at(L, y, nu);
+  nbr(L, x, mu, 0, nu, down ? -1 : 1, y);
+  const double2* pb = links.at(L, y, mu);
+  nbr(L, x, mu, 0, nu, down ? -1 : 0, y);
+  const double2* pc = links.at(L, y, nu);
+  double2 b[9], c[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) A[k] = make_double2(0, 0);
-#pragma unroll 1
-  for (int nu = 0; nu < 4; ++nu) {
-    if (nu == mu) continue;
-    double2 a[9], b[9], t[9], w[9];
-    int y[4];
-    nbr(L, x, mu, 1, nu, 0, y);
-    load_link(gv, L, y, nu, a);
-    nbr(L, x, mu, 0, nu, 1, y);
-    load_link(gv, L, y, mu, b);
-    m3(a, false, b, true, t);
-    load_link(gv, L, x, nu, a);
-    m3(t, false, a, true, w);
+  for (int k = 0; k < 9; ++k) b[k] = pb[S * k];
+  // c^dag (up) or c (down), as the right factor
 #pragma unroll
-    for (int k = 0; k < 9; ++k) A[k] = make_double2(A[k].x + w[k].x, A[k].y + w[k].y);
-    nbr(L, x, mu, 1, nu, -1, y);
-    load_link(gv, L, y, nu, a);
-    nbr(L, x, mu, 0, nu, -1, y);
-    load_link(gv, L, y, mu, b);
-    m3(a, true, b, true, t);
-    load_link(gv, L, y, nu, a);
-    m3(t, false, a, false, w);
+  for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int k = 0; k < 9; ++k) A[k] = make_double2(A[k].x + w[k].x, A[k].y + w[k].y);
+    for (int j = 0; j < 3; ++j) {
+      const double2 v = pc[S * (down ? 3 * i + j : 3 * j + i)];
+      c[3 * i + j] = make_double2(v.x, down ? v.y : -v.y);
+    }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    double2 a[3], t[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {   // row i of a (up) or a^dag (down)
+      const double2 v = pa[S * (down ? 3 * k + i : 3 * i + k)];
+      a[k] = make_double2(sign * v.x, sign * (down ? -v.y : v.y));
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      t[j] = make_double2(0, 0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {   // a_k conj(b_jk)
+        t[j].x += a[k].x * b[3 * j + k].x + a[k].y * b[3 * j + k].y;
+        t[j].y += a[k].y * b[3 * j + k].x - a[k].x * b[3 * j + k].y;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const double2 w = dmul(t[k], c[3 * k + j]);
+        A[3 * i + j].x += w.x;
+        A[3 * i + j].y += w.y;
+      }
   }
 }
 
@@ -629,10 +785,9 @@ __device__ __forceinline__ void quat_times(const double a[4], const double b[4],
 
 // Kennedy-Pendleton: x0 with density ~ sqrt(1 - x0^2) exp(alpha x0)
 __device__ double kp_sample(double alpha, LinkDraws& d) {
-  const double twopi = 2.0 * 3.14159265358979323846;
   for (int tries = 0; tries <= 10000; ++tries) {
     const double r1 = d.next(), r2 = d.next(), r3 = d.next(), r4 = d.next();
-    const double c = cos(twopi * r2);
+    const double c = cospi(2.0 * r2);
     const double lam2 = -(log(r1) + c * c * log(r3)) / (2.0 * alpha);
     if (r4 * r4 <= 1.0 - lam2) return 1.0 - 2.0 * lam2;
   }
@@ -640,7 +795,6 @@ __device__ double kp_sample(double alpha, LinkDraws& d) {
 }
 
 __device__ void level1_link(double2 U[9], const double2 A[9], double beta, int n_or, LinkDraws& d) {
-  const double twopi = 2.0 * 3.14159265358979323846;
   for (int pass = 0; pass <= n_or; ++pass)
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -664,9 +818,11 @@ __device__ void level1_link(double2 U[9], const double2 A[9], double beta, int n
       if (pass == 0) {
         const double x0 = kp_sample(2.0 * beta * norm / 3.0, d);
         const double rad = sqrt(fmax(0.0, 1.0 - x0 * x0));
-        const double ct = 2.0 * d.next() - 1.0, ph = twopi * d.next();
+        const double ct = 2.0 * d.next() - 1.0, ph = 2.0 * d.next();
         const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
-        const double X[4] = {x0, rad * st * cos(ph), rad * st * sin(ph), rad * ct};
+        double sn, cs;
+        sincospi(ph, &sn, &cs);
+        const double X[4] = {x0, rad * st * cs, rad * st * sn, rad * ct};
         quat_times(X, vd, R);
       } else {
         quat_times(vd, vd, R);  // over-relaxation keeps Re tr(R W)
@@ -715,50 +871,143 @@ __device__ void level1_link(double2 U[9], const double2 A[9], double beta, int n
   U[8] = cross(0, 4, 1, 3);
 }
 
-// One thread per link of the class: sites of parity `par` in slices
-// [t0, t1) (spatial directions: [t0 + 1, t1)), enumerated as pairs along x3.
-__global__ void __launch_bounds__(128) k_level1_class(GaugeView gv, double2* __restrict__ region, BlockSpec bs,
-                                                       int mu, int par, double beta, uint32_t k0, uint32_t k1,
-                                                       int sweep, int n_or) {
-  const int ta = gv.r_t0 + (mu != 0), t1 = gv.r_t1;  // frozen spatial links of the first slice
-  const int h3 = bs.L[3] / 2;
-  const size_t rows = (size_t)(t1 - ta) * bs.L[1] * bs.L[2];
-  const size_t n = rows * h3;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    int x[4];
+// One (direction, parity) class of a sweep: its links are those of the sites of
+// parity `par` in slices [t0, t1) (spatial directions: [t0 + 1, t1)), enumerated
+// as pairs along x3, 64 to a tile.  None of them enters another's staples.
+struct LinkClass {
+  int t0, t1, mu, par;
+  __host__ __device__ size_t size(const int L[4]) const {   // frozen spatial links of the first slice
+    return (size_t)(t1 - t0 - (mu != 0)) * L[1] * L[2] * (L[3] / 2);
+  }
+  __device__ __forceinline__ void site(const int L[4], size_t k, int x[4]) const {
+    const int h3 = L[3] / 2;
     size_t r = k / h3;
     const int j = (int)(k - r * h3);
-    x[2] = (int)(r % bs.L[2]); r /= bs.L[2];
-    x[1] = (int)(r % bs.L[1]);
-    x[0] = ta + (int)(r / bs.L[1]);
+    x[2] = (int)(r % L[2]); r /= L[2];
+    x[1] = (int)(r % L[1]);
+    x[0] = t0 + (mu != 0) + (int)(r / L[1]);
     x[3] = 2 * j + ((par + x[0] + x[1] + x[2]) & 1);
-    const size_t s = gidx(bs.L, x);
-    double2 A[9], U[9];
-    wilson_staples(gv, bs.L, x, mu, A);
-    load_link(gv, bs.L, x, mu, U);
-    LinkDraws d{k0, k1, (uint32_t)s, (uint32_t)(mu | (sweep << 2)), 0u, 0u, 0u, 0u, 0u, 0};
-    level1_link(U, A, beta, n_or, d);
-    double2* dst = region + ((s - (size_t)gv.r_t0 * bs.L[1] * bs.L[2] * bs.L[3]) * 4 + mu) * 9;
+  }
+};
+
+// Staple sums of a class, A[tile][9][64].  One workgroup per tile and one
+// wavefront per staple: a wavefront that adds up all six waits for one set of
+// loads after the other, and with a tile per wavefront the tiles in flight read
+// the links around them from beyond the L2 about twice.
+template <typename Links>
+__global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(4)))
+    k_level1_staples(Links links, BlockSpec bs, LinkClass cl, double2* __restrict__ out) {
+  __shared__ double2 sm[3][9][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int tile = xcd_chunk(blockIdx.x, gridDim.x);
+  const size_t k = (size_t)tile * 64 + lane;
+  double2 A[9];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) dst[c] = U[c];
+  for (int c = 0; c < 9; ++c) A[c] = make_double2(0, 0);
+  if (k < cl.size(bs.L)) {
+    int x[4];
+    cl.site(bs.L, k, x);
+    const int nu = w >> 1;
+    add_staple(links, bs.L, x, cl.mu, nu < cl.mu ? nu : nu + 1, w & 1, 1.0, A);
+  }
+  // (0 + 3) + (1 + 4) + (2 + 5), in this order
+  if (w >= 3)
+#pragma unroll
+    for (int c = 0; c < 9; ++c) sm[w - 3][c][lane] = A[c];
+  __syncthreads();
+  if (w < 3)
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+      const double2 v = sm[w][c][lane];
+      sm[w][c][lane] = make_double2(A[c].x + v.x, A[c].y + v.y);
+    }
+  __syncthreads();
+  for (int q = threadIdx.x; q < 9 * 64; q += 384) {
+    const double2 u = (&sm[0][0][0])[q], v = (&sm[1][0][0])[q], z = (&sm[2][0][0])[q];
+    out[(size_t)tile * 9 * 64 + q] = make_double2(u.x + v.x + z.x, u.y + v.y + z.y);
   }
 }
 
-hipError_t launch_level1_sweeps(const GaugeView& gv, double2* region, const BlockSpec& bs, double beta,
-                                uint64_t seed, uint32_t stream, int nsweeps, int n_or, hipStream_t st) {
-  const size_t n = (size_t)(gv.r_t1 - gv.r_t0) * bs.L[1] * bs.L[2] * bs.L[3] / 2;
-  size_t grid = (n + 127) / 128;
-  if (grid > 16384) grid = 16384;
+// The update of the links of a class, one per thread, from their staple sums;
+// without a place for those (staples null, canonical links) a thread adds up its
+// own.
+// On a 16 x 32^3 slab the staples of a class (262144 links) take 80 us, bound by
+// the links they read (0.3 GB at least), and the updates 39 us, bound by the
+// sampler's dependent FP64 operations (three waves per SIMD; four spill: 56 us).
+// In one kernel a class took 193 us from canonical links and 123 us from the
+// working copy, a wavefront for all six staples of its links, or 120 us with the
+// first of six wavefronts updating; working copy in and out 0.23 ms per call.
+template <typename Links>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+    k_level1_update(Links links, BlockSpec bs, LinkClass cl, const double2* __restrict__ staples, double beta,
+                    uint32_t k0, uint32_t k1, int sweep, int n_or) {
+  const int tile = xcd_chunk(blockIdx.x, gridDim.x);
+  const size_t k = (size_t)tile * 64 + threadIdx.x;
+  if (k >= cl.size(bs.L)) return;
+  int x[4];
+  cl.site(bs.L, k, x);
+  double2* own = links.at(bs.L, x, cl.mu);
+  double2 A[9], U[9];
+  if constexpr (std::is_same<Links, CanonLinks>::value) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) A[c] = make_double2(0, 0);
+#pragma unroll 1
+    for (int s = 0; s < 6; ++s)
+      add_staple(links, bs.L, x, cl.mu, (s >> 1) < cl.mu ? s >> 1 : (s >> 1) + 1, s & 1, 1.0, A);
+  } else {
+    const double2* st = staples + (size_t)tile * 9 * 64 + threadIdx.x;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) A[c] = st[64 * c];
+  }
+#pragma unroll
+  for (int c = 0; c < 9; ++c) U[c] = own[Links::kStep * c];
+  LinkDraws d{k0, k1, (uint32_t)gidx(bs.L, x), (uint32_t)(cl.mu | (sweep << 2)), 0u, 0u, 0u, 0u, 0u, 0};
+  level1_link(U, A, beta, n_or, d);
+#pragma unroll
+  for (int c = 0; c < 9; ++c) own[Links::kStep * c] = U[c];
+}
+
+size_t level1_staple_bytes(const BlockSpec& bs, int t0, int t1) {
+  return (LinkClass{t0, t1, 0, 0}.size(bs.L) + 63) / 64 * 9 * 64 * sizeof(double2);
+}
+
+template <typename Links>
+static hipError_t level1_classes(const Links& links, double2* staples, const BlockSpec& bs, int t0, int t1,
+                                 double beta, uint64_t seed, uint32_t stream, int nsweeps, int n_or, hipStream_t st) {
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32) ^ (stream * 0x85EBCA6Bu);
   for (int sweep = 0; sweep < nsweeps; ++sweep)
     for (int mu = 0; mu < 4; ++mu)
       for (int par = 0; par < 2; ++par) {
-        hipLaunchKernelGGL(k_level1_class, dim3((unsigned)grid), dim3(128), 0, st, gv, region, bs, mu, par, beta, k0,
-                           k1, sweep, n_or);
+        const LinkClass cl{t0, t1, mu, par};
+        const unsigned grid = (unsigned)((cl.size(bs.L) + 63) / 64);   // V <= 2^30: at most 2^23
+        if (grid == 0) continue;   // a slab of one slice has no free spatial links
+        if constexpr (!std::is_same<Links, CanonLinks>::value)
+          hipLaunchKernelGGL(k_level1_staples<Links>, dim3(grid), dim3(384), 0, st, links, bs, cl, staples);
+        hipLaunchKernelGGL(k_level1_update<Links>, dim3(grid), dim3(64), 0, st, links, bs, cl, staples, beta, k0, k1,
+                           sweep, n_or);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
   return hipSuccess;
+}
+
+// The slab's links and, when it is not the whole time extent, those of the
+// slice above it (the only ones outside that staples of its free links read)
+// are copied to `copy`, swept there and written back to the region.
+hipError_t launch_level1_slab(const GaugeView& parent, double2* region, const BoxLinks& copy, double2* staples,
+                              const BlockSpec& bs, int t0, int t1, double beta, uint64_t seed, uint32_t stream, int nsweeps, int n_or,
+                              hipStream_t st) {
+  hipError_t e = launch_box_links(parent, copy, bs, st);
+  if (e == hipSuccess) e = level1_classes(copy, staples, bs, t0, t1, beta, seed, stream, nsweeps, n_or, st);
+  if (e != hipSuccess) return e;
+  const int n = (t1 - t0) * bs.L[1] * bs.L[2] * bs.L[3];
+  hipLaunchKernelGGL(k_box_copy<false>, dim3((n + 63) / 64), dim3(256), 0, st, parent, region, bs, copy, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_level1_sweeps(const GaugeView& gv, const BlockSpec& bs, double beta, uint64_t seed, uint32_t stream,
+                                int nsweeps, int n_or, hipStream_t st) {
+  return level1_classes(CanonLinks{gv}, nullptr, bs, gv.r_t0, gv.r_t1, beta, seed, stream, nsweeps, n_or, st);
 }
 
 // 16-bit copies for the FP16-storage inner solver: links with scale 1 (their

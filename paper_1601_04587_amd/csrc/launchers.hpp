@@ -113,6 +113,21 @@ struct GaugeView {
   const double2* region;  // [V_region][4][9] override for time slices [r_t0, r_t1), may be null
   int r_t0, r_t1;
 };
+// Working copy of the FP64 links of a box of the lattice (origin o in [0, L),
+// extents E <= L, wrapping around the lattice): [mu][parity][tile][9][64], parities
+// and tiles those of the box.  at(): x is a lattice site inside the box.
+struct BoxLinks {
+  double2* W;
+  int o[4], E[4], nt;
+  static constexpr int kStep = 64;
+  __device__ double2* at(const int L[4], const int x[4], int mu) const;
+};
+size_t box_links_bytes(const BoxLinks& bl);
+// the boxes (W unset) that the clover term of a domain reads: one site more on
+// each side of its cut directions; and that a level-1 sweep of a slab reads
+BoxLinks clover_box(const BlockSpec& bs);
+BoxLinks level1_box(const BlockSpec& bs, int t0, int t1);
+hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const BlockSpec& bs, hipStream_t st);
 // FP64 links (5-pair layout) and the two-row FP32 copy; bit 2 of *bad if a link is not SU(3)
 hipError_t launch_build_links(const GaugeView& gv, const BlockSpec& bs, double2* U64, float2* U32, int* bad,
                               hipStream_t st);
@@ -127,9 +142,16 @@ hipError_t launch_gather(const double2* canon, const BlockSpec& bs, int p, int n
                          hipStream_t st);
 hipError_t launch_scatter(const double2* eo, const BlockSpec& bs, int p, int nrhs, double scale, double2* canon,
                           hipStream_t st);
-// level-1 updates of the region [gv.r_t0, gv.r_t1) of a gauge version (bs.L the lattice)
-hipError_t launch_level1_sweeps(const GaugeView& gv, double2* region, const BlockSpec& bs, double beta,
-                                uint64_t seed, uint32_t stream, int nsweeps, int n_or, hipStream_t st);
+// level-1 updates of the slab [t0, t1) (bs.L the lattice): from the parent's links
+// to the version's region, through a working copy of level1_box and a buffer of
+// level1_staple_bytes for the staple sums of one class of links
+size_t level1_staple_bytes(const BlockSpec& bs, int t0, int t1);
+hipError_t launch_level1_slab(const GaugeView& parent, double2* region, const BoxLinks& copy, double2* staples,
+                              const BlockSpec& bs, int t0, int t1, double beta, uint64_t seed, uint32_t stream, int nsweeps, int n_or,
+                              hipStream_t st);
+// the same without the two, on a region [gv.r_t0, gv.r_t1) that holds the parent's links
+hipError_t launch_level1_sweeps(const GaugeView& gv, const BlockSpec& bs, double beta, uint64_t seed, uint32_t stream,
+                                int nsweeps, int n_or, hipStream_t st);
 // out = scale * D_{dGamma} in on canonical [nrhs][V][12] fields, Gamma = [bs.lo, bs.lo + bs.Lb)
 hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
                            double scale, hipStream_t st);
