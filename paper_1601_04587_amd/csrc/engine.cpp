@@ -459,8 +459,6 @@ std::shared_ptr<OpBlock> opblock(Ctx* c, int gauge_id, int dom_id) {
   ob->A64 = DBuf(c->pool.get(), kCloverSlots * ns * sizeof(double2));
   ob->Ainv64 = DBuf(c->pool.get(), kCloverSlots * ns * sizeof(double2));
   ob->Ainv32 = DBuf(c->pool.get(), kCloverSlots * ns * sizeof(float2));
-  for (DBuf* b : {&ob->U64, &ob->U32, &ob->A64, &ob->Ainv64, &ob->Ainv32})
-    DDML_HIP(hipMemsetAsync(b->p, 0, b->bytes, c->stream));
   ob->walks = walks_of(c, ob->g, ob->tps);
   GaugeView gv;
   gv.base = git->second.base->as<double2>();
@@ -468,9 +466,12 @@ std::shared_ptr<OpBlock> opblock(Ctx* c, int gauge_id, int dom_id) {
   gv.r_t0 = git->second.r_t0;
   gv.r_t1 = git->second.r_t1;
   DDML_HIP(hipMemsetAsync(c->flag.p, 0, sizeof(int), c->stream));
-  DDML_HIP(launch_build_links(gv, ob->bs, ob->U64.as<double2>(), ob->U32.as<float2>(), c->flag.as<int>(), c->stream));
-  DDML_HIP(launch_build_clover(gv, ob->bs, ob->A64.as<double2>(), ob->Ainv64.as<double2>(), ob->Ainv32.as<float2>(),
-                               c->flag.as<int>(), c->stream));
+  BoxLinks copy = clover_box(ob->bs);
+  DBuf work = scratch(c, box_links_bytes(copy));
+  copy.W = work.as<double2>();
+  DDML_HIP(launch_build_block(gv, work.p ? &copy : nullptr, ob->bs, ob->g, ob->U64.as<double2>(), ob->U32.as<float2>(),
+                              ob->A64.as<double2>(), ob->Ainv64.as<double2>(), ob->Ainv32.as<float2>(),
+                              c->flag.as<int>(), c->stream));
   int* hf = (int*)pinned_area(c, sizeof(int));
   DDML_HIP(hipMemcpyAsync(hf, c->flag.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   DDML_HIP(hipStreamSynchronize(c->stream));

@@ -187,44 +187,55 @@ hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const Block
 // conjugate of the cross product of the first two, times the face factor
 // (+-1; 0 zeroes all rows).  That holds for SU(3) matrices only: a link whose
 // third row differs from the rebuilt one by more than 1e-5 sets bit 2 of *bad.
-__global__ void k_build_links(GaugeView gv, BlockSpec bs, double2* __restrict__ U64, float2* __restrict__ U32,
-                              int* __restrict__ bad) {
-  const int Vb = bs.Lb[0] * bs.Lb[1] * bs.Lb[2] * bs.Lb[3];
-  const int nt = ntiles_of(bs);
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < Vb; s += gridDim.x * blockDim.x) {
+// One wavefront per (parity, 64-site tile, direction); padding sites are zeroed.
+template <typename Links>
+__global__ void __launch_bounds__(256) k_build_links(Links links, BlockSpec bs, BoxGeom g, double2* __restrict__ U64,
+                                                     float2* __restrict__ U32, int* __restrict__ bad) {
+  const int nt = g.ntiles;
+  const int item = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (item >= 8 * nt) return;
+  const int mu = item & 3, tile = (item >> 2) % nt, p = (item >> 2) / nt;
+  const int i = tile * kTile + lane;
+  double2 u[10];
+#pragma unroll
+  for (int k = 0; k < 10; ++k) u[k] = make_double2(0, 0);   // entry 9 is the zero pad of the last pair
+  if (i < g.Vh) {
     int y[4], x[4];
-    lex_coords(bs.Lb, s, y);
+    eo_coords(g, p, i, y);
+#pragma unroll
     for (int m = 0; m < 4; ++m) x[m] = bs.lo[m] + y[m];
-    const int p = (y[0] + y[1] + y[2] + y[3]) & 1;
-    const int i = s >> 1;
-    for (int mu = 0; mu < 4; ++mu) {
-      double2 u[9];
-      load_link(gv, bs.L, x, mu, u);
-      double f = 1.0;
-      if (y[mu] == bs.Lb[mu] - 1) {
-        if (bs.Lb[mu] != bs.L[mu]) f = 0.0;                  // Dirichlet face of the domain
-        else if (mu == 0 && bs.tbc == 1) f = -1.0;          // antiperiodic wrap in time
-        else if (mu == 0 && bs.tbc == 2) f = 0.0;           // open: no hop across the time boundary
-      }
+    const double2* src = links.at(bs.L, x, mu);
 #pragma unroll
-      for (int k = 0; k < 10; ++k) {  // entry 9 is the zero pad of the last pair
-        const double2 v = k < 9 ? make_double2(f * u[k].x, f * u[k].y) : make_double2(0, 0);
-        if (U64) U64[lidx(nt, p, mu, k, i)] = v;
-        if (U32 && k < 6) U32[lidx2(nt, p, mu, k, i)] = make_float2((float)v.x, (float)v.y);
-      }
-      // third row against conj(row 0 x row 1)
-      double dev = 0;
+    for (int k = 0; k < 9; ++k) u[k] = src[Links::kStep * k];
+    // third row against conj(row 0 x row 1)
+    double dev = 0;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int a = (q + 1) % 3, b = (q + 2) % 3;
-        const double2 x1 = u[a], y1 = u[3 + b], x2 = u[b], y2 = u[3 + a];
-        const double cr = (x1.x * y1.x - x1.y * y1.y) - (x2.x * y2.x - x2.y * y2.y);
-        const double ci = (x1.x * y1.y + x1.y * y1.x) - (x2.x * y2.y + x2.y * y2.x);
-        dev = fmax(dev, fabs(u[6 + q].x - cr) + fabs(u[6 + q].y + ci));
-      }
-      if (!(dev <= 1e-5)) atomicOr(bad, 2);
+    for (int q = 0; q < 3; ++q) {
+      const int a = (q + 1) % 3, b = (q + 2) % 3;
+      const double2 x1 = u[a], y1 = u[3 + b], x2 = u[b], y2 = u[3 + a];
+      const double cr = (x1.x * y1.x - x1.y * y1.y) - (x2.x * y2.x - x2.y * y2.y);
+      const double ci = (x1.x * y1.y + x1.y * y1.x) - (x2.x * y2.y + x2.y * y2.x);
+      dev = fmax(dev, fabs(u[6 + q].x - cr) + fabs(u[6 + q].y + ci));
     }
+    if (!(dev <= 1e-5)) atomicOr(bad, 2);
+    const int ym = mu == 0 ? y[0] : (mu == 1 ? y[1] : (mu == 2 ? y[2] : y[3]));
+    const int Lb = mu == 0 ? g.L[0] : (mu == 1 ? g.L[1] : (mu == 2 ? g.L[2] : g.L[3]));
+    const int Ll = mu == 0 ? bs.L[0] : (mu == 1 ? bs.L[1] : (mu == 2 ? bs.L[2] : bs.L[3]));
+    double f = 1.0;
+    if (ym == Lb - 1) {
+      if (Lb != Ll) f = 0.0;                          // Dirichlet face of the domain
+      else if (mu == 0 && bs.tbc == 1) f = -1.0;      // antiperiodic wrap in time
+      else if (mu == 0 && bs.tbc == 2) f = 0.0;       // open: no hop across the time boundary
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) u[k] = make_double2(f * u[k].x, f * u[k].y);
   }
+#pragma unroll
+  for (int k = 0; k < 5; ++k) st2nt(U64 + lidx(nt, p, mu, 2 * k, i), u[2 * k], u[2 * k + 1]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    st2nt(U32 + lidx2(nt, p, mu, 2 * k, i), make_float2((float)u[2 * k].x, (float)u[2 * k].y),
+          make_float2((float)u[2 * k + 1].x, (float)u[2 * k + 1].y));
 }
 
 // --------------------------------------------------------------- SU(3) FP64
@@ -234,23 +245,6 @@ __device__ __forceinline__ double2 dmul(double2 a, double2 b) {
 __device__ __forceinline__ double2 dmulc(double2 a, double2 b) {  // conj(a) b
   return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
-// c = a b, with optional adjoints of a and b
-__device__ __forceinline__ void m3(const double2 a[9], bool da, const double2 b[9], bool db, double2 c[9]) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = make_double2(0, 0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        double2 ak = da ? make_double2(a[3 * k + i].x, -a[3 * k + i].y) : a[3 * i + k];
-        double2 bk = db ? make_double2(b[3 * j + k].x, -b[3 * j + k].y) : b[3 * k + j];
-        s = make_double2(s.x + ak.x * bk.x - ak.y * bk.y, s.y + ak.x * bk.y + ak.y * bk.x);
-      }
-      c[3 * i + j] = s;
-    }
-}
-
 // y = x + dmu mu + dnu nu (periodic gauge field), without indexing x by mu
 __device__ __forceinline__ void nbr(const int L[4], const int x[4], int mu, int dmu, int nu, int dnu, int y[4]) {
 #pragma unroll
@@ -260,65 +254,105 @@ __device__ __forceinline__ void nbr(const int L[4], const int x[4], int mu, int 
   }
 }
 
-// acc <- acc U_dir(x + dmu mu + dnu nu)  (or its adjoint)
-__device__ __forceinline__ void leaf_step(const GaugeView& gv, const int L[4], const int x[4], int mu, int dmu,
-                                          int nu, int dnu, int dir, bool dag, double2 acc[9]) {
+// A += sign times one staple of U_mu(x) in the (mu, nu) plane:
+//   up    U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
+//   down  U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
+// row by row, so that two of its three links and A are live.
+template <typename Links>
+__device__ __forceinline__ void add_staple(const Links& links, const int L[4], const int x[4], int mu, int nu,
+                                           bool down, double sign, double2 A[9]) {
+  constexpr int S = Links::kStep;
   int y[4];
-  nbr(L, x, mu, dmu, nu, dnu, y);
-  double2 u[9], t[9];
-  load_link(gv, L, y, dir, u);
-  m3(acc, false, u, dag, t);
+  nbr(L, x, mu, 1, nu, down ? -1 : 0, y);
+  const double2* pa = links.at(L, y, nu);
+  nbr(L, x, mu, 0, nu, down ? -1 : 1, y);
+  const double2* pb = links.at(L, y, mu);
+  nbr(L, x, mu, 0, nu, down ? -1 : 0, y);
+  const double2* pc = links.at(L, y, nu);
+  double2 b[9], c[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) acc[k] = t[k];
-}
-
-// Fhat_{mu nu}(x) = (Q - Q^dag)/8 with Q the sum of the four counter-clockwise
-// leaves at x, each built link by link:
-//   U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-//   U_nu(x) U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu)
-//   U_mu(x-mu)^dag U_nu(x-mu-nu)^dag U_mu(x-mu-nu) U_nu(x-nu)
-//   U_nu(x-nu)^dag U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^dag
-__device__ __forceinline__ void field_strength(const GaugeView& gv, const int L[4], const int x[4], int mu, int nu,
-                                               double2 F[9]) {
-  double2 Q[9], acc[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) Q[k] = make_double2(0, 0);
-#pragma unroll 1
-  for (int leaf = 0; leaf < 4; ++leaf) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) acc[k] = make_double2(k % 4 == 0 ? 1.0 : 0.0, 0.0);
-    if (leaf == 0) {
-      leaf_step(gv, L, x, mu, 0, nu, 0, mu, false, acc);
-      leaf_step(gv, L, x, mu, 1, nu, 0, nu, false, acc);
-      leaf_step(gv, L, x, mu, 0, nu, 1, mu, true, acc);
-      leaf_step(gv, L, x, mu, 0, nu, 0, nu, true, acc);
-    } else if (leaf == 1) {
-      leaf_step(gv, L, x, mu, 0, nu, 0, nu, false, acc);
-      leaf_step(gv, L, x, mu, -1, nu, 1, mu, true, acc);
-      leaf_step(gv, L, x, mu, -1, nu, 0, nu, true, acc);
-      leaf_step(gv, L, x, mu, -1, nu, 0, mu, false, acc);
-    } else if (leaf == 2) {
-      leaf_step(gv, L, x, mu, -1, nu, 0, mu, true, acc);
-      leaf_step(gv, L, x, mu, -1, nu, -1, nu, true, acc);
-      leaf_step(gv, L, x, mu, -1, nu, -1, mu, false, acc);
-      leaf_step(gv, L, x, mu, 0, nu, -1, nu, false, acc);
-    } else {
-      leaf_step(gv, L, x, mu, 0, nu, -1, nu, true, acc);
-      leaf_step(gv, L, x, mu, 0, nu, -1, mu, false, acc);
-      leaf_step(gv, L, x, mu, 1, nu, -1, nu, false, acc);
-      leaf_step(gv, L, x, mu, 0, nu, 0, mu, true, acc);
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      Q[k].x += acc[k].x;
-      Q[k].y += acc[k].y;
-    }
-  }
+  for (int k = 0; k < 9; ++k) b[k] = pb[S * k];
+  // c^dag (up) or c (down), as the right factor
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const double2 v = pc[S * (down ? 3 * i + j : 3 * j + i)];
+      c[3 * i + j] = make_double2(v.x, down ? v.y : -v.y);
+    }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    double2 a[3], t[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {   // row i of a (up) or a^dag (down)
+      const double2 v = pa[S * (down ? 3 * k + i : 3 * i + k)];
+      a[k] = make_double2(sign * v.x, sign * (down ? -v.y : v.y));
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      t[j] = make_double2(0, 0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {   // a_k conj(b_jk)
+        t[j].x += a[k].x * b[3 * j + k].x + a[k].y * b[3 * j + k].y;
+        t[j].y += a[k].y * b[3 * j + k].x - a[k].x * b[3 * j + k].y;
+      }
+    }
+#pragma unroll
     for (int j = 0; j < 3; ++j)
-      F[3 * i + j] = make_double2((Q[3 * i + j].x - Q[3 * j + i].x) * 0.125, (Q[3 * i + j].y + Q[3 * j + i].y) * 0.125);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const double2 w = dmul(t[k], c[3 * k + j]);
+        A[3 * i + j].x += w.x;
+        A[3 * i + j].y += w.y;
+      }
+  }
+}
+
+// Fhat_{mu nu}(x) = (Q - Q^dag)/8, Q the sum of the four counter-clockwise
+// leaves at x.  With D(x) the up staple of U_mu(x) minus the down one, two of
+// the leaves and the adjoints of the others make Q - Q^dag = Z - Z^dag with
+//   Z = U_mu(x) D(x) + D(x-mu) U_mu(x-mu):
+// ten 3x3 products instead of the twelve of four leaves.  Z - Z^dag is
+// anti-Hermitian and kept as nine numbers: F[0..2] the imaginary diagonal, then
+// entries (0,1), (0,2), (1,2).
+template <typename Links>
+__device__ __forceinline__ void field_strength(const Links& links, const int L[4], const int x[4], int mu, int nu,
+                                               double F[9]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) F[k] = 0;
+#pragma unroll 1
+  for (int back = 0; back < 2; ++back) {
+    int y[4];
+    nbr(L, x, mu, -back, nu, 0, y);
+    double2 D[9], u[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) D[k] = make_double2(0, 0);
+#pragma unroll 1
+    for (int down = 0; down < 2; ++down) add_staple(links, L, y, mu, nu, down, down ? -0.125 : 0.125, D);
+    const double2* pu = links.at(L, y, mu);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) u[k] = pu[Links::kStep * k];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        double2 z = make_double2(0, 0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const double2 l = back ? D[3 * i + k] : u[3 * i + k], r = back ? u[3 * k + j] : D[3 * k + j];
+          const double2 w = dmul(l, r);
+          z.x += w.x;
+          z.y += w.y;
+        }
+        if (i == j) {
+          F[i] += 2 * z.y;
+        } else {
+          const int e = 3 + 2 * (i + j - 1);   // pair (0,1), (0,2) or (1,2)
+          F[e] += i < j ? z.x : -z.x;
+          F[e + 1] += z.y;
+        }
+      }
+  }
 }
 
 // A Hermitian 6x6 block is kept packed: the real diagonal d[6] and the 15
@@ -328,97 +362,96 @@ __device__ __forceinline__ constexpr int up_idx(int r, int c) { return r * (11 -
 __device__ __forceinline__ constexpr int lo_idx(int i, int j) { return i * (i - 1) / 2 + j; }
 
 // Clover term of every site of the box, as the two chiral 6x6 blocks of
-//   A = 1 + sum_l s_l (x) X_l^{+-},  X_l^{+-} = i kappa c_sw (+-Fhat_{0l} - B_l),
-// accumulated plane by plane so that only one Fhat and the packed block are
-// live: the (0,l) planes enter X_l with +-1, (2,3) enters X_1 with -1, (1,3)
-// X_2 with +1 (B_2 = Fhat_31 = -Fhat_13) and (1,2) X_3 with -1.  s_3 puts X_3
-// on the diagonal spin blocks with + and -, s_1 and s_2 put X_1 - i X_2 on
-// the upper off-diagonal spin block.
-__global__ void __launch_bounds__(128) k_build_clover(GaugeView gv, BlockSpec bs, double2* __restrict__ A64) {
-  const int Vb = bs.Lb[0] * bs.Lb[1] * bs.Lb[2] * bs.Lb[3];
-  const int nt = ntiles_of(bs);
+//   A = 1 + sum_l s_l (x) X_l^{+-},  X_l^{+-} = i kappa c_sw (+-Fhat_{0l} - B_l).
+// A workgroup is one 64-site tile of a parity and six wavefronts, one per plane
+// (0,1) (0,2) (0,3) (2,3) (1,3) (1,2): each leaves its Fhat in LDS, then wavefront
+// b packs block b.  s_3 puts X_3 on the diagonal spin blocks with + and -, s_1
+// and s_2 put X_1 - i X_2 on the upper off-diagonal spin block.
+// Bound by its chain of link loads (three waves per SIMD): 24^3 x 16 takes 0.30 ms
+// with the working copy (0.07 ms to make); 0.52 ms with the nine complex numbers
+// of Fhat, which spill, and parity by parity over the box; 0.81 ms when a thread
+// built both blocks of a site from canonical links, every plane twice.
+template <typename Links>
+__global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(3)))
+    k_build_clover(Links links, BlockSpec bs, BoxGeom g, double2* __restrict__ A64) {
+  __shared__ double Fs[6][9][kTile];
+  const int nt = g.ntiles, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int id = xcd_chunk(blockIdx.x, 2 * nt);
+  const int p = id & 1, tile = id >> 1;
+  const int i = tile * kTile + lane;
   const double c = bs.kappa * bs.csw;
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < Vb; s += gridDim.x * blockDim.x) {
+  double F[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) F[k] = 0;
+  if (i < g.Vh && c != 0.0) {
     int y[4], x[4];
-    lex_coords(bs.Lb, s, y);
+    eo_coords(g, p, i, y);
+#pragma unroll
     for (int m = 0; m < 4; ++m) x[m] = bs.lo[m] + y[m];
-    const int p = (y[0] + y[1] + y[2] + y[3]) & 1;
-    const int i = s >> 1;
-#pragma unroll 1
-    for (int blk = 0; blk < 2; ++blk) {
-      const double sg = blk == 0 ? 1.0 : -1.0;
-      double dg[6];
-      double2 up[15];
+    const int mu = w < 3 ? 0 : (w == 3 ? 2 : 1);
+    const int nu = w < 3 ? w + 1 : (w == 5 ? 2 : 3);
+    field_strength(links, bs.L, x, mu, nu, F);
+  }
 #pragma unroll
-      for (int k = 0; k < 6; ++k) dg[k] = 1.0;
+  for (int k = 0; k < 9; ++k) Fs[w][k][lane] = F[k];
+  __syncthreads();
+  if (w >= 2) return;
+  const double sg = w == 0 ? 1.0 : -1.0, one = i < g.Vh ? 1.0 : 0.0;   // padding sites hold zeros
+  // number k of +-Fhat_{0l} - B_l: B_1 = Fhat_23, B_2 = -Fhat_13, B_3 = Fhat_12
+  auto f = [&](int l, int k) { return sg * Fs[l][k][lane] + (l == 1 ? 1.0 : -1.0) * Fs[3 + l][k][lane]; };
+  // entry (a, b) of X_{l+1} = i c (...)
+  auto X = [&](int l, int a, int b) {
+    if (a == b) return make_double2(-c * f(l, a), 0.0);
+    const int e = 3 + 2 * (a + b - 1);
+    const double x = f(l, e), y = f(l, e + 1);
+    return make_double2(-c * y, a < b ? c * x : -c * x);
+  };
+  double dg[6];
+  double2 up[15];
 #pragma unroll
-      for (int k = 0; k < 15; ++k) up[k] = make_double2(0, 0);
-      if (c != 0.0) {
-#pragma unroll 1
-        for (int pl = 0; pl < 6; ++pl) {
-          const int mu = pl < 3 ? 0 : (pl == 5 ? 1 : (pl == 3 ? 2 : 1));
-          const int nu = pl < 3 ? pl + 1 : (pl == 5 ? 2 : 3);
-          const int l = pl < 3 ? pl : pl - 3;                       // X_{l+1}
-          const double f = pl < 3 ? sg : (pl == 4 ? 1.0 : -1.0);
-          double2 F[9];
-          field_strength(gv, bs.L, x, mu, nu, F);
-          // contribution i c f Fhat to X_{l+1}
-          double2 Z[9];
+  for (int a = 0; a < 3; ++a) {
+    const double d = X(2, a, a).x;
+    dg[a] = one + d;
+    dg[3 + a] = one - d;
 #pragma unroll
-          for (int k = 0; k < 9; ++k) Z[k] = make_double2(-c * f * F[k].y, c * f * F[k].x);
-          if (l == 2) {
+    for (int b = a + 1; b < 3; ++b) {
+      const double2 z = X(2, a, b);
+      up[up_idx(a, b)] = z;
+      up[up_idx(3 + a, 3 + b)] = make_double2(-z.x, -z.y);
+    }
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-              dg[a] += Z[4 * a].x;
-              dg[3 + a] -= Z[4 * a].x;
-#pragma unroll
-              for (int b2 = a + 1; b2 < 3; ++b2) {
-                const double2 z = Z[3 * a + b2];
-                up[up_idx(a, b2)].x += z.x;
-                up[up_idx(a, b2)].y += z.y;
-                up[up_idx(3 + a, 3 + b2)].x -= z.x;
-                up[up_idx(3 + a, 3 + b2)].y -= z.y;
-              }
-            }
-          } else {
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-              for (int b2 = 0; b2 < 3; ++b2) {
-                const double2 z = Z[3 * a + b2];
-                double2& u = up[up_idx(a, 3 + b2)];
-                if (l == 0) {            // + X_1
-                  u.x += z.x;
-                  u.y += z.y;
-                } else {                 // - i X_2
-                  u.x += z.y;
-                  u.y -= z.x;
-                }
-              }
-          }
-        }
-      }
-      A64[cidx(nt, p, 18 * blk + 0, i)] = make_double2(dg[0], dg[1]);
-      A64[cidx(nt, p, 18 * blk + 1, i)] = make_double2(dg[2], dg[3]);
-      A64[cidx(nt, p, 18 * blk + 2, i)] = make_double2(dg[4], dg[5]);
-#pragma unroll
-      for (int k = 0; k < 15; ++k) A64[cidx(nt, p, 18 * blk + 3 + k, i)] = up[k];
+    for (int b = 0; b < 3; ++b) {
+      const double2 z1 = X(0, a, b), z2 = X(1, a, b);
+      up[up_idx(a, 3 + b)] = make_double2(z1.x + z2.y, z1.y - z2.x);
     }
   }
+  double2* A = A64 + cidx(nt, p, 18 * w, i);
+  st2(A, make_double2(dg[0], dg[1]), make_double2(dg[2], dg[3]));
+  st2(A + 128, make_double2(dg[4], dg[5]), up[0]);
+#pragma unroll
+  for (int k = 0; k < 7; ++k) st2(A + 128 * (2 + k), up[1 + 2 * k], up[2 + 2 * k]);
 }
 
 // Inverse of each packed block by Cholesky A = L L^dag in FP64:
 //   L_jj = sqrt(A_jj - sum_{k<j} |L_jk|^2),  L_ij = (A_ij - sum_{k<j} L_ik conj(L_jk)) / L_jj,
 //   W = L^{-1} (lower),  A^{-1} = W^dag W.
 // One thread per (parity, block, site); a non-positive pivot sets *bad.
+// Padding sites are zeroed.
 __global__ void __launch_bounds__(128) k_invert_clover(const double2* __restrict__ A64, int nt, int Vh,
                                                        double2* __restrict__ Ainv64, float2* __restrict__ Ainv32,
                                                        int* __restrict__ bad) {
-  const size_t n = (size_t)4 * Vh;
+  const size_t per = (size_t)nt * kTile, n = 4 * per;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(t % Vh);
-    const int pb = (int)(t / Vh);
+    const int i = (int)(t % per);
+    const int pb = (int)(t / per);
     const int p = pb >> 1, blk = pb & 1;
+    if (i >= Vh) {
+      for (int k = 0; k < 18; ++k) {
+        Ainv64[cidx(nt, p, 18 * blk + k, i)] = make_double2(0, 0);
+        Ainv32[cidx(nt, p, 18 * blk + k, i)] = make_float2(0, 0);
+      }
+      continue;
+    }
     double ad[6];
     double2 au[15];
 #pragma unroll
@@ -488,8 +521,8 @@ __global__ void __launch_bounds__(128) k_invert_clover(const double2* __restrict
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const double2 v = make_double2(idg[2 * k], idg[2 * k + 1]);
-      if (Ainv64) Ainv64[cidx(nt, p, 18 * blk + k, i)] = v;
-      if (Ainv32) Ainv32[cidx(nt, p, 18 * blk + k, i)] = make_float2((float)v.x, (float)v.y);
+      Ainv64[cidx(nt, p, 18 * blk + k, i)] = v;
+      Ainv32[cidx(nt, p, 18 * blk + k, i)] = make_float2((float)v.x, (float)v.y);
     }
 #pragma unroll
     for (int r = 0; r < 6; ++r)
@@ -502,30 +535,35 @@ __global__ void __launch_bounds__(128) k_invert_clover(const double2* __restrict
           acc.x += q.x;
           acc.y += q.y;
         }
-        if (Ainv64) Ainv64[cidx(nt, p, 18 * blk + 3 + up_idx(r, cc), i)] = acc;
-        if (Ainv32) Ainv32[cidx(nt, p, 18 * blk + 3 + up_idx(r, cc), i)] = make_float2((float)acc.x, (float)acc.y);
+        Ainv64[cidx(nt, p, 18 * blk + 3 + up_idx(r, cc), i)] = acc;
+        Ainv32[cidx(nt, p, 18 * blk + 3 + up_idx(r, cc), i)] = make_float2((float)acc.x, (float)acc.y);
       }
   }
 }
 
-hipError_t launch_build_links(const GaugeView& gv, const BlockSpec& bs, double2* U64, float2* U32, int* bad,
-                              hipStream_t st) {
-  const int Vb = bs.Lb[0] * bs.Lb[1] * bs.Lb[2] * bs.Lb[3];
-  int grid = (Vb + 255) / 256;
-  if (grid > 16384) grid = 16384;
-  hipLaunchKernelGGL(k_build_links, dim3(grid), dim3(256), 0, st, gv, bs, U64, U32, bad);
+template <typename Links>
+static hipError_t build_block(const Links& links, const BlockSpec& bs, const BoxGeom& g, double2* U64, float2* U32,
+                              double2* A64, int* bad, hipStream_t st) {
+  hipLaunchKernelGGL(k_build_links<Links>, dim3(2 * g.ntiles), dim3(256), 0, st, links, bs, g, U64, U32, bad);
+  hipLaunchKernelGGL(k_build_clover<Links>, dim3(2 * g.ntiles), dim3(384), 0, st, links, bs, g, A64);
   return hipGetLastError();
 }
-hipError_t launch_build_clover(const GaugeView& gv, const BlockSpec& bs, double2* A64, double2* Ainv64,
-                               float2* Ainv32, int* bad, hipStream_t st) {
-  const int Vb = bs.Lb[0] * bs.Lb[1] * bs.Lb[2] * bs.Lb[3];
-  int grid = (Vb + 127) / 128;
+
+hipError_t launch_build_block(const GaugeView& gv, const BoxLinks* copy, const BlockSpec& bs, const BoxGeom& g,
+                              double2* U64, float2* U32, double2* A64, double2* Ainv64, float2* Ainv32, int* bad,
+                              hipStream_t st) {
+  hipError_t e = hipSuccess;
+  if (copy) {
+    e = launch_box_links(gv, *copy, bs, st);
+    if (e == hipSuccess) e = build_block(*copy, bs, g, U64, U32, A64, bad, st);
+  } else {
+    e = build_block(CanonLinks{gv}, bs, g, U64, U32, A64, bad, st);
+  }
+  if (e != hipSuccess) return e;
+  size_t grid = ((size_t)4 * g.ntiles * kTile + 127) / 128;
   if (grid > 16384) grid = 16384;
-  hipLaunchKernelGGL(k_build_clover, dim3(grid), dim3(128), 0, st, gv, bs, A64);
-  const int Vh = Vb / 2;
-  int grid2 = (4 * Vh + 127) / 128;
-  if (grid2 > 16384) grid2 = 16384;
-  hipLaunchKernelGGL(k_invert_clover, dim3(grid2), dim3(128), 0, st, A64, ntiles_of(bs), Vh, Ainv64, Ainv32, bad);
+  hipLaunchKernelGGL(k_invert_clover, dim3((unsigned)grid), dim3(128), 0, st, A64, g.ntiles, g.Vh, Ainv64, Ainv32,
+                     bad);
   return hipGetLastError();
 }
 
@@ -721,60 +759,6 @@ struct LinkDraws {
     return ((double)w + 1.0) * (1.0 / 4294967296.0);
   }
 };
-
-// A += sign times one staple of U_mu(x) in the (mu, nu) plane:
-//   up    U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-//   down  U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-// row by row, so that two of its three links and A are live.
-template <typename Links>
-__device__ __forceinline__ void add_staple(const Links& links, const int L[4], const int x[4], int mu, int nu,
-                                           bool down, double sign, double2 A[9]) {
-  constexpr int S = Links::kStep;
-  int y[4];
-  nbr(L, x, mu, 1, nu, down ? -1 : 0, y);
-  const double2* pa = links.at(L, y, nu);
-  nbr(L, x, mu, 0, nu, down ? -1 : 1, y);
-  const double2* pb = links.at(L, y, mu);
-  nbr(L, x, mu, 0, nu, down ? -1 : 0, y);
-  const double2* pc = links.at(L, y, nu);
-  double2 b[9], c[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) b[k] = pb[S * k];
-  // c^dag (up) or c (down), as the right factor
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const double2 v = pc[S * (down ? 3 * i + j : 3 * j + i)];
-      c[3 * i + j] = make_double2(v.x, down ? v.y : -v.y);
-    }
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    double2 a[3], t[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {   // row i of a (up) or a^dag (down)
-      const double2 v = pa[S * (down ? 3 * k + i : 3 * i + k)];
-      a[k] = make_double2(sign * v.x, sign * (down ? -v.y : v.y));
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      t[j] = make_double2(0, 0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {   // a_k conj(b_jk)
-        t[j].x += a[k].x * b[3 * j + k].x + a[k].y * b[3 * j + k].y;
-        t[j].y += a[k].y * b[3 * j + k].x - a[k].x * b[3 * j + k].y;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double2 w = dmul(t[k], c[3 * k + j]);
-        A[3 * i + j].x += w.x;
-        A[3 * i + j].y += w.y;
-      }
-  }
-}
 
 __device__ __forceinline__ void quat_times(const double a[4], const double b[4], double c[4]) {
   c[0] = a[0] * b[0] - a[1] * b[1] - a[2] * b[2] - a[3] * b[3];

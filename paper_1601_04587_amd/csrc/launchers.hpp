@@ -128,11 +128,12 @@ size_t box_links_bytes(const BoxLinks& bl);
 BoxLinks clover_box(const BlockSpec& bs);
 BoxLinks level1_box(const BlockSpec& bs, int t0, int t1);
 hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const BlockSpec& bs, hipStream_t st);
-// FP64 links (5-pair layout) and the two-row FP32 copy; bit 2 of *bad if a link is not SU(3)
-hipError_t launch_build_links(const GaugeView& gv, const BlockSpec& bs, double2* U64, float2* U32, int* bad,
+// Operator block: FP64 links (5-pair layout) and the two-row FP32 copy (bit 2 of
+// *bad if a link is not SU(3)), clover term and inverse (bit 1 if a block has
+// none).  copy: where to put the working copy of clover_box, or null.
+hipError_t launch_build_block(const GaugeView& gv, const BoxLinks* copy, const BlockSpec& bs, const BoxGeom& g,
+                              double2* U64, float2* U32, double2* A64, double2* Ainv64, float2* Ainv32, int* bad,
                               hipStream_t st);
-hipError_t launch_build_clover(const GaugeView& gv, const BlockSpec& bs, double2* A64, double2* Ainv64,
-                               float2* Ainv32, int* bad, hipStream_t st);
 // 16-bit copies of an operator block's links (from the two-row FP32 copy, n complex
 // numbers) and A^{-1} (2 * ntiles * 64 sites)
 hipError_t launch_quant_links(const float2* U32, h16c* U16, size_t n, hipStream_t st);

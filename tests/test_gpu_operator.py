@@ -1,4 +1,4 @@
-"""GPU: the operator on canonical fields and the boundary block
+"""GPU: the operator on canonical fields, its operator block and the boundary block
 where their kernels can go wrong: boxes cut in every direction, rows and boxes that
 fill no whole wavefront or tile, every number of columns, inputs that are also the
 output, and contexts without room for the working copy of the links.
