@@ -928,8 +928,10 @@ hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk
   // groups of six columns at most (what two waves per SIMD have registers for),
   // as even as they come
   const int groups = (nrhs + 5) / 6;
-  int grid = ntl * groups < 16384 ? ntl * groups : 16384;
-  grid = (grid + kXcd - 1) / kXcd * kXcd;
+  // (a small box may lie on few XCDs: a workgroup for each of the longest list)
+  int longest = 0;
+  for (int x = 0; x < kXcd; ++x) longest = xoff[x + 1] - xoff[x] > longest ? xoff[x + 1] - xoff[x] : longest;
+  const int grid = kXcd * (longest * groups < 2048 ? longest * groups : 2048);
 #define DDML_DW(Rv)                                                                                                 \
   case Rv:                                                                                                          \
     hipLaunchKernelGGL(k_apply_d<Rv>, dim3(grid), dim3(256), 0, st, g, bs, w, U, A, in, out, nrhs, ntl, rows);      \
