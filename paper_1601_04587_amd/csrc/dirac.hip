@@ -874,15 +874,15 @@ __device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, c
 }
 
 // Clears the part outside Gamma of rows [r0, r1) of the field's nrhs L0 L1 L2
-// rows of L3 sites, one wave per row.
-__device__ __forceinline__ void clear_rows(const BoxGeom& g, const BlockSpec& bs, double2* __restrict__ out, long r0,
-                                           long r1) {
+// rows of L3 sites (fewer than 2^31 in 288 GB), one wave per row.
+__device__ __forceinline__ void clear_rows(const BoxGeom& g, const BlockSpec& bs, double2* __restrict__ out,
+                                           unsigned r0, unsigned r1) {
   const int lane = threadIdx.x & 63;
-  for (long r = r0 + (threadIdx.x >> 6); r < r1; r += blockDim.x >> 6) {
-    long q = r;
-    const int x2 = (int)(q % bs.L[2]) - bs.lo[2]; q /= bs.L[2];
-    const int x1 = (int)(q % bs.L[1]) - bs.lo[1]; q /= bs.L[1];
-    const int x0 = (int)(q % bs.L[0]) - bs.lo[0];
+  for (unsigned r = r0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); r < r1; r += blockDim.x >> 6) {
+    const unsigned q = r / (unsigned)bs.L[2];
+    const int x2 = (int)(r - q * bs.L[2]) - bs.lo[2];
+    const unsigned p = q / (unsigned)bs.L[1];
+    const int x1 = (int)(q - p * bs.L[1]) - bs.lo[1], x0 = (int)(p % (unsigned)bs.L[0]) - bs.lo[0];
     const bool crosses = (unsigned)x0 < (unsigned)g.L[0] && (unsigned)x1 < (unsigned)g.L[1] &&
                          (unsigned)x2 < (unsigned)g.L[2];
     if (crosses && g.L[3] == bs.L[3]) continue;
