@@ -949,6 +949,109 @@ hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk
   return hipGetLastError();
 }
 
+// ------------------------------------------------- boundary block D_{dGamma}
+// The entries of D that join a site x of the domain Gamma to a neighbour y
+// outside it (eq. blkdec; the off-diagonal block of eq. Scmpt2):
+//   y = x + mu:  -1/2 (1 - gamma_mu) U_mu(x) psi(y)
+//   y = x - mu:  -1/2 (1 + gamma_mu) U_mu(y)^dag psi(y)
+// with the time-boundary phase (antiperiodic -1, open: no such hop), on
+// canonical fields and links.  Nearly all of the output is zero: a wavefront takes
+// a row of L3 sites, and one that no coupling reaches is only cleared, in
+// contiguous streaming stores.  The rest go through the quads of lanes of
+// k_apply_d, 16 sites at a time, a lane's site taking the hops that leave Gamma.
+// Bound by the stores: 12 columns of a 32^3 x 32 field, one face of 32^3, 467 us
+// for 2.4 GB, 700 with a thread per site.  (Plain stores 480 us.  A fill in 4 KB
+// workgroups takes 345, but the faces in a launch of their own 100 more, and a
+// launch more is 4 us on a small field.)
+__device__ __forceinline__ const double2* canon_link(const GaugeView& gv, const BlockSpec& bs, size_t site, int t,
+                                                     int mu) {
+  if (gv.region && t >= gv.r_t0 && t < gv.r_t1)
+    return gv.region + ((site - (size_t)gv.r_t0 * bs.L[1] * bs.L[2] * bs.L[3]) * 4 + mu) * 9;
+  return gv.base + (site * 4 + mu) * 9;
+}
+
+__device__ __forceinline__ void boundary_site(const GaugeView& gv, const BlockSpec& bs, const int x[4], int spin,
+                                              const double2* __restrict__ in, double scale, double2 out[3]) {
+  const double sg1 = spin < 2 ? 1.0 : -1.0, sg2 = (spin == 0 || spin == 3) ? 1.0 : -1.0;
+  double2 acc[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) acc[a] = make_double2(0, 0);
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      const bool fwd = dir == 0;
+      // a hop leaves Gamma at the last (first) site of a cut direction only
+      const int edge = fwd ? bs.lo[mu] + bs.Lb[mu] - 1 : bs.lo[mu];
+      if (bs.Lb[mu] == bs.L[mu] || x[mu] != edge) continue;   // (the four lanes of a site together)
+      int y[4] = {x[0], x[1], x[2], x[3]};
+      y[mu] += fwd ? 1 : -1;
+      double ph = -0.5 * scale;
+      if (y[mu] < 0 || y[mu] >= bs.L[mu]) {
+        y[mu] = fwd ? 0 : bs.L[mu] - 1;
+        if (mu == 0 && bs.tbc == 2) continue;
+        if (mu == 0 && bs.tbc == 1) ph = -ph;
+      }
+      const size_t sy = (((size_t)y[0] * bs.L[1] + y[1]) * bs.L[2] + y[2]) * bs.L[3] + y[3];
+      const size_t sx = (((size_t)x[0] * bs.L[1] + x[1]) * bs.L[2] + x[2]) * bs.L[3] + x[3];
+      const double2* ug = canon_link(gv, bs, fwd ? sx : sy, fwd ? x[0] : y[0], mu);
+      double2 raw[3], psi[3], h[3], u[9];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) raw[j] = ldg2(in + sy * 12 + 4 * j + spin);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) u[k] = ldg2(ug + k);
+      quad_to_spin(spin, raw, psi);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) h[a] = cscale(spin_term(mu, fwd, psi[a], sg1, sg2), ph);
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          acc[a] = fwd ? cmac(acc[a], u[3 * a + b], h[b]) : cmacc(acc[a], u[3 * b + a], h[b]);
+    }
+  spin_to_quad(spin, acc, out);
+}
+
+__global__ void __launch_bounds__(256) k_boundary(GaugeView gv, BlockSpec bs, const double2* __restrict__ in,
+                                                  double2* __restrict__ out, unsigned rows, double scale) {
+  const int lane = threadIdx.x & 63, L3 = bs.L[3];
+  const size_t vol = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * L3 * 12;
+  for (unsigned row = blockIdx.x * 4 + (threadIdx.x >> 6); row < rows; row += gridDim.x * 4) {
+    int x[4] = {0, 0, 0, 0};
+    unsigned q = __builtin_amdgcn_readfirstlane(row);
+    x[2] = (int)(q % (unsigned)bs.L[2]); q /= (unsigned)bs.L[2];
+    x[1] = (int)(q % (unsigned)bs.L[1]); q /= (unsigned)bs.L[1];
+    x[0] = (int)(q % (unsigned)bs.L[0]);
+    const size_t col = q / (unsigned)bs.L[0];
+    bool in_row = true, face = bs.Lb[3] != bs.L[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      in_row = in_row && x[m] >= bs.lo[m] && x[m] < bs.lo[m] + bs.Lb[m];
+      face = face || (bs.Lb[m] != bs.L[m] && (x[m] == bs.lo[m] || x[m] == bs.lo[m] + bs.Lb[m] - 1));
+    }
+    double2* const o = out + (size_t)row * L3 * 12;
+    if (!(in_row && face)) {   // (uniform over the wavefront)
+      for (int k = lane; k < 12 * L3; k += 64) stg2nt(o + k, make_double2(0, 0));
+      continue;
+    }
+    for (int s = lane >> 2; s < L3; s += 16) {
+      x[3] = s;
+      double2 v[3] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
+      if (s >= bs.lo[3] && s < bs.lo[3] + bs.Lb[3]) boundary_site(gv, bs, x, lane & 3, in + col * vol, scale, v);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) stg2nt(o + s * 12 + 4 * j + (lane & 3), v[j]);
+    }
+  }
+}
+
+hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
+                           double scale, hipStream_t st) {
+  const unsigned rows = (unsigned)nrhs * bs.L[0] * bs.L[1] * bs.L[2];   // (fewer than 2^31 in 288 GB)
+  const unsigned grid = (rows + 3) / 4 < 65536 ? (rows + 3) / 4 : 65536;
+  hipLaunchKernelGGL(k_boundary, dim3(grid), dim3(256), 0, st, gv, bs, in, out, rows, scale);
+  return hipGetLastError();
+}
+
 // Batched launch over solver slots.  Linear order: virtual tile vt of the
 // batch maps to (slot, tile) through tile_start[nslots+1].  Other orders:
 // XCD x walks xstart[x][*], the prefix over slots of its share of the tiles.

@@ -33,12 +33,6 @@ __device__ __forceinline__ const double2* link_ptr(const GaugeView& gv, const in
   return gv.base + (s * 4 + mu) * 9;
 }
 
-__device__ __forceinline__ void load_link(const GaugeView& gv, const int L[4], const int x[4], int mu, double2 u[9]) {
-  const double2* p = link_ptr(gv, L, x, mu);
-#pragma unroll
-  for (int k = 0; k < 9; ++k) u[k] = p[k];
-}
-
 // local lexicographic index -> local coords
 __device__ __forceinline__ void lex_coords(const int Lb[4], int s, int y[4]) {
   y[3] = s % Lb[3]; s /= Lb[3];
@@ -610,110 +604,6 @@ __global__ void k_scatter(const double2* __restrict__ eo, BlockSpec bs, int p, i
     }
   }
 }
-// ------------------------------------------------- boundary block D_{dGamma}
-// The entries of D that join a site x of the domain Gamma to a neighbour y
-// outside it (eq. blkdec; the off-diagonal block of eq. Scmpt2):
-//   y = x + mu:  -1/2 (1 - gamma_mu) U_mu(x) psi(y)
-//   y = x - mu:  -1/2 (1 + gamma_mu) U_mu(y)^dag psi(y)
-// with the time-boundary phase (antiperiodic -1, open: no such hop).  One
-// thread per (column, site) of the canonical field; sites outside Gamma and
-// inner sites write zero.  Each row of a chiral-basis gamma matrix has a
-// single entry: (gamma_mu psi)_a = ph_mu(a) psi_{col_mu(a)}, with
-//   col: a ^ 2 for mu = 0, 3 and 3 - a for mu = 1, 2;
-//   ph:  -1 (mu 0); -i, -i, +i, +i (mu 1); -1, +1, +1, -1 (mu 2); -i, +i, +i, -i (mu 3).
-__device__ __forceinline__ constexpr int gam_col(int mu, int a) { return (mu == 0 || mu == 3) ? (a ^ 2) : 3 - a; }
-__device__ __forceinline__ constexpr double gam_re(int mu, int a) {
-  return mu == 0 ? -1.0 : (mu == 2 ? ((a == 0 || a == 3) ? -1.0 : 1.0) : 0.0);
-}
-__device__ __forceinline__ constexpr double gam_im(int mu, int a) {
-  return mu == 1 ? (a < 2 ? -1.0 : 1.0) : (mu == 3 ? ((a == 0 || a == 3) ? -1.0 : 1.0) : 0.0);
-}
-
-__device__ __forceinline__ bool in_box(const BlockSpec& bs, const int x[4]) {
-  bool in = true;
-#pragma unroll
-  for (int m = 0; m < 4; ++m) in = in && x[m] >= bs.lo[m] && x[m] < bs.lo[m] + bs.Lb[m];
-  return in;
-}
-
-__global__ void __launch_bounds__(256) k_boundary(GaugeView gv, BlockSpec bs, const double2* __restrict__ in, double2* __restrict__ out,
-                           int nrhs, double scale) {
-  const size_t V = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * bs.L[3];
-  const size_t n = V * nrhs;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    const size_t site = k % V, col = k / V;
-    int x[4];
-    size_t r = site;
-    x[3] = (int)(r % bs.L[3]); r /= bs.L[3];
-    x[2] = (int)(r % bs.L[2]); r /= bs.L[2];
-    x[1] = (int)(r % bs.L[1]);
-    x[0] = (int)(r / bs.L[1]);
-    double2 acc[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = make_double2(0, 0);
-    if (in_box(bs, x)) {
-#pragma unroll
-      for (int mu = 0; mu < 4; ++mu)
-#pragma unroll
-        for (int d = 1; d >= -1; d -= 2) {
-          int y[4] = {x[0], x[1], x[2], x[3]};
-          y[mu] += d;
-          double ph = -0.5 * scale;
-          if (y[mu] < 0 || y[mu] >= bs.L[mu]) {
-            y[mu] = (y[mu] + bs.L[mu]) % bs.L[mu];
-            if (mu == 0 && bs.tbc == 2) continue;
-            if (mu == 0 && bs.tbc == 1) ph = -ph;
-          }
-          if (in_box(bs, y)) continue;
-          double2 u[9];
-          load_link(gv, bs.L, d > 0 ? x : y, mu, u);
-          const double2* psi = in + (col * V + gidx(bs.L, y)) * 12;
-          double2 chi[12];  // U psi or U^dag psi, per spin component
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-              double2 t = make_double2(0, 0);
-#pragma unroll
-              for (int j = 0; j < 3; ++j) {
-                const double2 v = psi[3 * a + j];
-                const double2 w = d > 0 ? dmul(u[3 * i + j], v) : dmulc(u[3 * j + i], v);
-                t.x += w.x;
-                t.y += w.y;
-              }
-              chi[3 * a + i] = t;
-            }
-#pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            const int b = gam_col(mu, a);
-            const double gr = gam_re(mu, a), gi = gam_im(mu, a);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-              const double2 v = chi[3 * b + i];
-              // (1 - d gamma_mu) chi
-              const double2 t = make_double2(chi[3 * a + i].x - d * (gr * v.x - gi * v.y),
-                                             chi[3 * a + i].y - d * (gr * v.y + gi * v.x));
-              acc[3 * a + i].x += ph * t.x;
-              acc[3 * a + i].y += ph * t.y;
-            }
-          }
-        }
-    }
-    double2* o = out + (col * V + site) * 12;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) o[c] = acc[c];
-  }
-}
-
-hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
-                           double scale, hipStream_t st) {
-  const size_t n = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * bs.L[3] * nrhs;
-  size_t grid = (n + 255) / 256;
-  if (grid > 32768) grid = 32768;
-  hipLaunchKernelGGL(k_boundary, dim3((unsigned)grid), dim3(256), 0, st, gv, bs, in, out, nrhs, scale);
-  return hipGetLastError();
-}
-
 // ----------------------------------------------------------- level-1 updates
 // Quenched updates of the links of the slab [t0, t1) of a gauge version with
 // the spatial links of slice t0 fixed (the level-1 updates of the two-level

@@ -13,6 +13,13 @@ struct BlockSpec {
   double kappa, csw;
 };
 
+// The links of a gauge version.
+struct GaugeView {
+  const double2* base;    // [V][4][9] canonical FP64 links of the whole lattice
+  const double2* region;  // [V_region][4][9] override for time slices [r_t0, r_t1), may be null
+  int r_t0, r_t1;
+};
+
 // dirac.hip
 hipError_t launch_hop_item(const HopItem<double2>& it, int mode, int red, int R, int order, hipStream_t st);
 // xstart: [kXcd][xstride] per-XCD prefix of tile counts (all orders but linear);
@@ -39,6 +46,9 @@ inline int band_count(int ntiles, int tps, int x) {
 // (walk, xoff: the box's lexicographic 64-site tiles by XCD)
 hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk, const int* xoff, const double2* U,
                           const double2* A, const double2* in, double2* out, int nrhs, hipStream_t st);
+// out = scale * D_{dGamma} in on canonical [nrhs][V][12] fields, Gamma = [bs.lo, bs.lo + bs.Lb)
+hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
+                           double scale, hipStream_t st);
 hipError_t launch_clover_apply(const BoxGeom& g, const double2* clov, int p, const double2* in, double2* out,
                                int nrhs, hipStream_t st);
 
@@ -108,11 +118,6 @@ hipError_t launch_sum_partials(const double2* partial, int nred, int nrhs, int n
                                int accumulate, hipStream_t st);
 
 // gauge.hip: operator blocks
-struct GaugeView {
-  const double2* base;    // [V][4][9] canonical FP64 links of the whole lattice
-  const double2* region;  // [V_region][4][9] override for time slices [r_t0, r_t1), may be null
-  int r_t0, r_t1;
-};
 // Working copy of the FP64 links of a box of the lattice (origin o in [0, L),
 // extents E <= L, wrapping around the lattice): [mu][parity][tile][9][64], parities
 // and tiles those of the box.  at(): x is a lattice site inside the box.
@@ -153,9 +158,6 @@ hipError_t launch_level1_slab(const GaugeView& parent, double2* region, const Bo
 // the same without the two, on a region [gv.r_t0, gv.r_t1) that holds the parent's links
 hipError_t launch_level1_sweeps(const GaugeView& gv, const BlockSpec& bs, double beta, uint64_t seed, uint32_t stream,
                                 int nsweeps, int n_or, hipStream_t st);
-// out = scale * D_{dGamma} in on canonical [nrhs][V][12] fields, Gamma = [bs.lo, bs.lo + bs.Lb)
-hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
-                           double scale, hipStream_t st);
 
 // contract.hip
 hipError_t launch_series_diff(double2* terms, size_t n, int nlevels, double2* sum, hipStream_t st, int ncol = 0,
