@@ -346,7 +346,7 @@ template <typename T2> struct HopItem {
   int par_out;
   int nrhs;
   int ntiles;
-  double c1, c2;
+  double c1;
   int tps;            // tiles per time slice (banded tile order), 0 = linear order
   const int* walk;    // tile walk of the sub-banded orders (all tiles, XCD-major), may be null
   int xoff[kXcd + 1]; // XCD x walks walk[xoff[x] .. xoff[x+1])
@@ -355,10 +355,9 @@ template <typename T2> struct HopItem {
 // Stencil epilogues (acc = H in on the output parity):
 //   MODE_CINV_HOP  out = C acc                       (C = A^{-1}_pp)
 //   MODE_SCHUR     out = aux - c1 C acc              (c1 = kappa^2: the Schur operator)
-//   MODE_M         out = c2 (C aux - c1 acc)         (C = A_pp, c1 = kappa: M = A - kappa H)
 //   MODE_PREP      out = C (aux + c1 acc)            (C = A^{-1}_pp: EO prepare/reconstruct)
 //   MODE_RES       out = red_a - (C aux - c1 acc)    (residual b - M x)
-enum { MODE_CINV_HOP = 0, MODE_SCHUR = 1, MODE_M = 2, MODE_PREP = 3, MODE_RES = 4 };
+enum { MODE_CINV_HOP = 0, MODE_SCHUR = 1, MODE_PREP = 2, MODE_RES = 3 };
 // Fused reductions (FP64 partial sums per 64-site tile and column, written to
 // partial slot k at [k][nrhs][ntiles]):
 //   RED_DOT  slot 0: (h, out), h the shadow vector below

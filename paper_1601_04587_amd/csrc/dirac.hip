@@ -464,9 +464,9 @@ __device__ __forceinline__ double2 wave_sum(double2 v) {
 // Epilogue on one column.  acc = (H in)(x); cl points at slot 0 of this site.
 template <typename T2, int MODE, bool ST>
 __device__ __forceinline__ void epilogue_block(const T2* cl, int b, const T2 acc[6], const T2 aux[6], const T2 ra[6],
-                                               double c1, double c2, T2 out[6]) {
+                                               double c1, T2 out[6]) {
   using T = decltype(T2::x);
-  const T k1 = (T)c1, k2 = (T)c2;
+  const T k1 = (T)c1;
   T2 m[18];
   const T2* cb = cl + 128 * 9 * b;
   if (!ST) herm6_load(cb, m);
@@ -481,14 +481,11 @@ __device__ __forceinline__ void epilogue_block(const T2* cl, int b, const T2 acc
     apply(acc, y);
 #pragma unroll
     for (int c = 0; c < 6; ++c) out[c] = cmas(aux[c], y[c], -k1);
-  } else if (MODE == MODE_M || MODE == MODE_RES) {
+  } else if (MODE == MODE_RES) {
     T2 y[6];
     apply(aux, y);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      T2 v = cmas(y[c], acc[c], -k1);
-      out[c] = (MODE == MODE_M) ? cscale(v, k2) : csub(ra[c], v);
-    }
+    for (int c = 0; c < 6; ++c) out[c] = csub(ra[c], cmas(y[c], acc[c], -k1));
   } else {  // MODE_PREP: out = C (aux + c1 acc)
     T2 v[6];
 #pragma unroll
@@ -501,10 +498,10 @@ __device__ __forceinline__ void epilogue_block(const T2* cl, int b, const T2 acc
 // points at slot 0 of this site's clover data).
 template <typename T2, int MODE, bool ST>
 __device__ __forceinline__ void epilogue(const T2* cl, const T2 acc[12], const T2 aux[12],
-                                         const T2 ra[12], double c1, double c2, T2 out[12]) {
+                                         const T2 ra[12], double c1, T2 out[12]) {
 #pragma unroll
   for (int b = 0; b < 2; ++b)
-    epilogue_block<T2, MODE, ST>(cl, b, acc + 6 * b, aux + 6 * b, ra + 6 * b, c1, c2, out + 6 * b);
+    epilogue_block<T2, MODE, ST>(cl, b, acc + 6 * b, aux + 6 * b, ra + 6 * b, c1, out + 6 * b);
 }
 
 // The fused reductions of one output column over its components [c0, c0 + N)
@@ -554,7 +551,7 @@ template <typename E> struct TileArgs {
 // stored vectors.
 template <typename E, int R, int MODE, int RED, bool ST = false, typename C = typename CompOf<E>::type>
 __device__ __forceinline__ void hop_tile(const BoxGeom g, const TileArgs<E>& a, double2* __restrict__ partial,
-                                         const int* __restrict__ act, int p, int nrhs, double c1, double c2, int tile,
+                                         const int* __restrict__ act, int p, int nrhs, double c1, int tile,
                                          int wave0 = 0, const C* sm = nullptr) {
   const int lane = threadIdx.x & 63;
   const int grp = wave0 + (threadIdx.x >> 6);
@@ -597,7 +594,7 @@ __device__ __forceinline__ void hop_tile(const BoxGeom g, const TileArgs<E>& a, 
         const size_t qb = qidx(nt, col, i);
         if (MODE != MODE_CINV_HOP) spinor_load_q(a.aux + qb, ldgf(a.aux_n + ns), w, RED != RED_TS);
         if (MODE == MODE_RES) spinor_load_q(a.red_a + qb, ldgf(a.red_n + ns), ra, true);
-        epilogue<C, MODE, ST>(cl, acc[r], w, ra, c1, c2, w);
+        epilogue<C, MODE, ST>(cl, acc[r], w, ra, c1, w);
         spinor_store_q(a.out + qb, a.out_n + ns, w, w, true);
         if constexpr (RED == RED_TS) {
           C av[12];
@@ -616,7 +613,7 @@ __device__ __forceinline__ void hop_tile(const BoxGeom g, const TileArgs<E>& a, 
             if (MODE != MODE_CINV_HOP) ld2nt(a.aux + base + 128 * (3 * b + k), av[2 * k], av[2 * k + 1]);
             if (MODE == MODE_RES) ld2nt(a.red_a + base + 128 * (3 * b + k), ra[2 * k], ra[2 * k + 1]);
           }
-          epilogue_block<C, MODE, ST>(cl, b, acc[r] + 6 * b, av, ra, c1, c2, o);
+          epilogue_block<C, MODE, ST>(cl, b, acc[r] + 6 * b, av, ra, c1, o);
 #pragma unroll
           for (int k = 0; k < 3; ++k) st2nt(a.out + base + 128 * (3 * b + k), o[2 * k], o[2 * k + 1]);
           fused_reductions<RED, 6>(hb, 6 * b, o, av, s0, s1, s2);
@@ -674,11 +671,11 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
     }
     for (int v = j; v < total; v += nb) {
       const int tile = order == TILE_ORDER_BANDED ? band_tile(S, lo, bs, v) : ldg(it.walk + it.xoff[x] + v);
-      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, it.active, it.par_out, it.nrhs, it.c1, it.c2, tile);
+      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, it.active, it.par_out, it.nrhs, it.c1, tile);
     }
   } else {
     for (int tile = blockIdx.x; tile < it.ntiles; tile += gridDim.x)
-      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, it.active, it.par_out, it.nrhs, it.c1, it.c2, tile);
+      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, it.active, it.par_out, it.nrhs, it.c1, tile);
   }
 }
 
@@ -1122,7 +1119,7 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R))
     if constexpr (ST) stage_tile<T2>(d.g, d.U, clov, ta.clov_n, par_out, tile, sm);
     // c1: kappa^2 in the Schur operator, kappa in the FP64 residual and preparation
     const double c1 = (MODE == MODE_PREP || MODE == MODE_RES) ? d.kappa : d.kappa * d.kappa;
-    hop_tile<T2, R, MODE, RED, ST>(d.g, ta, d.partial, d.active, par_out, d.nrhs, c1, 0.0, tile, grp * W, sm);
+    hop_tile<T2, R, MODE, RED, ST>(d.g, ta, d.partial, d.active, par_out, d.nrhs, c1, tile, grp * W, sm);
     if constexpr (ST) __syncthreads();
   }
 }
