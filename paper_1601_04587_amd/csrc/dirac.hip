@@ -555,13 +555,22 @@ template <typename E> struct TileArgs {
   float* out_n;
 };
 
+// The columns that are active as a mask: lane c loads the flag of column c, so
+// that one load serves the workgroup's test and every wave's own (a load of its
+// own for each was two more trips to memory per tile).
+__device__ __forceinline__ int active_flag(const int* active, int nrhs) {
+  const int lane = threadIdx.x & 63;
+  return active == nullptr ? 1 : ldg(active + min(lane, nrhs - 1));
+}
+__device__ __forceinline__ unsigned active_of(int flag) { return (unsigned)__ballot(flag != 0); }
+
 // One tile on the output parity p.  ST: the tile's links and clover data are
 // staged in LDS at sm (stage_tile) and taken from there.  16-bit outputs are
 // quantised before the fused reductions, so the dot products are those of the
 // stored vectors.
 template <typename E, int R, int MODE, int RED, bool ST = false, typename C = typename CompOf<E>::type>
 __device__ __forceinline__ void hop_tile(const BoxGeom g, const TileArgs<E>& a, double2* __restrict__ partial,
-                                         const int* __restrict__ act, int p, int nrhs, double c1, int tile,
+                                         unsigned act, int p, int nrhs, double c1, int tile,
                                          int wave0 = 0, const C* sm = nullptr) {
   const int lane = threadIdx.x & 63;
   const int grp = wave0 + (threadIdx.x >> 6);
@@ -574,7 +583,7 @@ __device__ __forceinline__ void hop_tile(const BoxGeom g, const TileArgs<E>& a, 
   unsigned on = 0;  // active columns of this wavefront
 #pragma unroll
   for (int r = 0; r < R; ++r)
-    if (r < nr && (act == nullptr || ldg(act + r0 + r))) on |= 1u << r;
+    if (r < nr && ((act >> (r0 + r)) & 1u)) on |= 1u << r;
   if (on == 0) return;  // uniform across the wave
   C acc[R][12];
   if (valid) hop_sum<E, R, ST>(g, p, i, a.U, sm, a.in, a.in_n, r0, nr, on, acc);
@@ -669,6 +678,7 @@ __device__ __forceinline__ int band_tile(int S, int lo, int bs, int local) {
 // Single-item launch (operator application, outer FP64 steps).
 template <typename T2, int R, int MODE, int RED>
 __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopItem<T2> it, int order) {
+  const unsigned act = active_of(active_flag(it.active, it.nrhs));
   const TileArgs<T2> ta{it.U, it.clov, nullptr, it.in, nullptr, it.aux, nullptr, it.red_a, nullptr, it.out, nullptr};
   if (order != TILE_ORDER_LINEAR) {
     const int x = blockIdx.x % kXcd, j = blockIdx.x / kXcd, nb = gridDim.x / kXcd;
@@ -681,11 +691,11 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
     }
     for (int v = j; v < total; v += nb) {
       const int tile = order == TILE_ORDER_BANDED ? band_tile(S, lo, bs, v) : ldg(it.walk + it.xoff[x] + v);
-      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, it.active, it.par_out, it.nrhs, it.c1, tile);
+      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, act, it.par_out, it.nrhs, it.c1, tile);
     }
   } else {
     for (int tile = blockIdx.x; tile < it.ntiles; tile += gridDim.x)
-      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, it.active, it.par_out, it.nrhs, it.c1, tile);
+      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, act, it.par_out, it.nrhs, it.c1, tile);
   }
 }
 
@@ -1103,6 +1113,7 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R))
     const int tv = v / ng, grp = v - tv * ng;
     const int s = find_slot(P, ns, tv);
     const SlotDesc<T2>& d = slots[s];
+    const int flag = active_flag(d.active, d.nrhs);   // on its way with the walk's entry
     int tile = tv - P[s];
     if (order == TILE_ORDER_BANDED) {
       int S, lo, bs;
@@ -1111,14 +1122,11 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R))
     } else if (order != TILE_ORDER_LINEAR) {
       tile = ldg(d.walk + d.xoff[x] + tile);
     }
-    // a workgroup whose columns are all inactive skips the tile (uniform: every
-    // thread reads the same flags), before the staging
-    {
-      const int c0 = grp * W * R, c1 = min(d.nrhs, c0 + W * R);
-      bool any = false;
-      for (int c = c0; c < c1; ++c) any = any || ldg(d.active + c);
-      if (!any) continue;
-    }
+    // a workgroup whose columns are all inactive skips the tile before the staging
+    // (uniform: every wave reads the same flags)
+    const unsigned act = active_of(flag);
+    const int c0 = grp * W * R, c1 = min(d.nrhs, c0 + W * R);
+    if (c0 >= c1 || !((act >> c0) & ((1u << (c1 - c0)) - 1u))) continue;
     const bool h16 = kIs16<T2>;
     const T2* clov = MODE == MODE_RES ? d.A : d.Ainv;   // M = A - kappa H needs A itself
     const TileArgs<T2> ta{d.U, clov, h16 ? d.Ainv_nrm : nullptr,
@@ -1127,9 +1135,9 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R))
                           fred >= 0 ? d.f[fred] : nullptr, h16 && fred >= 0 ? d.nrm[fred] : nullptr,
                           d.f[fout], h16 ? d.nrm[fout] : nullptr};
     if constexpr (ST) stage_tile<T2>(d.g, d.U, clov, ta.clov_n, par_out, tile, sm);
-    // c1: kappa^2 in the Schur operator, kappa in the FP64 residual and preparation
-    const double c1 = (MODE == MODE_PREP || MODE == MODE_RES) ? d.kappa : d.kappa * d.kappa;
-    hop_tile<T2, R, MODE, RED, ST>(d.g, ta, d.partial, d.active, par_out, d.nrhs, c1, tile, grp * W, sm);
+    // kappa^2 in the Schur operator, kappa in the FP64 residual and preparation
+    const double kap = (MODE == MODE_PREP || MODE == MODE_RES) ? d.kappa : d.kappa * d.kappa;
+    hop_tile<T2, R, MODE, RED, ST>(d.g, ta, d.partial, act, par_out, d.nrhs, kap, tile, grp * W, sm);
     if constexpr (ST) __syncthreads();
   }
 }
