@@ -342,7 +342,6 @@ template <typename T2> struct HopItem {
   const T2* red_a;    // first operand of a fused dot product, may be null
   T2* out;            // output field on the output parity
   double2* partial;   // fused reduction partials [nred][nrhs][ntiles], may be null
-  const int* active;  // per-rhs flag, may be null (all active)
   int par_out;
   int nrhs;
   int ntiles;

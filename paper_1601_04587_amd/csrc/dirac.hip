@@ -560,7 +560,7 @@ template <typename E> struct TileArgs {
 // own for each was two more trips to memory per tile).
 __device__ __forceinline__ int active_flag(const int* active, int nrhs) {
   const int lane = threadIdx.x & 63;
-  return active == nullptr ? 1 : ldg(active + min(lane, nrhs - 1));
+  return ldg(active + min(lane, nrhs - 1));
 }
 __device__ __forceinline__ unsigned active_of(int flag) { return (unsigned)__ballot(flag != 0); }
 
@@ -675,10 +675,20 @@ __device__ __forceinline__ int band_tile(int S, int lo, int bs, int local) {
   return (local / bs) * S + lo + local % bs;
 }
 
-// Single-item launch (operator application, outer FP64 steps).
+// Single-item launch (apply_eo in FP64, outer FP64 steps).  Every column is
+// active, by a mask that the compiler does not see and that is set anew for each
+// tile: from a constant, or a mask made before the loop over tiles, it moves loads
+// of the epilogue above the hops and spills (47 to 1517 registers with a constant,
+// 59, 62 and 63 at R = 1 with a mask per launch; 0, 10 and 10 this way).  Bound
+// by links and clover data that every wave reads itself, it takes the same time with
+// those 60 registers spilled (24^3 x 16: 0.212 ms with 1 column, 1.51 with 12).
+__device__ __forceinline__ unsigned all_columns() {
+  unsigned m;
+  asm volatile("s_mov_b32 %0, -1" : "=s"(m));
+  return m;
+}
 template <typename T2, int R, int MODE, int RED>
 __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopItem<T2> it, int order) {
-  const unsigned act = active_of(active_flag(it.active, it.nrhs));
   const TileArgs<T2> ta{it.U, it.clov, nullptr, it.in, nullptr, it.aux, nullptr, it.red_a, nullptr, it.out, nullptr};
   if (order != TILE_ORDER_LINEAR) {
     const int x = blockIdx.x % kXcd, j = blockIdx.x / kXcd, nb = gridDim.x / kXcd;
@@ -691,11 +701,11 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
     }
     for (int v = j; v < total; v += nb) {
       const int tile = order == TILE_ORDER_BANDED ? band_tile(S, lo, bs, v) : ldg(it.walk + it.xoff[x] + v);
-      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, act, it.par_out, it.nrhs, it.c1, tile);
+      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, all_columns(), it.par_out, it.nrhs, it.c1, tile);
     }
   } else {
     for (int tile = blockIdx.x; tile < it.ntiles; tile += gridDim.x)
-      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, act, it.par_out, it.nrhs, it.c1, tile);
+      hop_tile<T2, R, MODE, RED>(it.g, ta, it.partial, all_columns(), it.par_out, it.nrhs, it.c1, tile);
   }
 }
 
