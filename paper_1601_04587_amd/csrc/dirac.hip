@@ -14,6 +14,7 @@
 // instead of HBM.  Domain restriction comes from zeroed face links, so the
 // inner loop has no masking branch.  Tiles are visited either linearly or in
 // XCD bands (see ddml_common.hpp) so that neighbour tiles share an L2.
+#include <algorithm>
 #include <type_traits>
 
 // No implicit contraction of a multiply and an add into one FMA in this file:
@@ -718,8 +719,8 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
 // ((1 -+ g_mu) psi)_s = psi_s -+ ph psi_{s'} with s' = s ^ 2 or 3 - s, and every lane
 // multiplies its own colour vector by the link, which is twice the SU(3) products
 // of the half-spinor form and no reconstruction.  A lane keeps R columns, so
-// that a link is read once for all of them.  Every workgroup also clears its
-// share of the rows outside Gamma: those stores wait for nothing.
+// that a link is read once for all of them.  The rows outside Gamma are cleared by
+// the same workgroups or by others of the launch (kShareTiles).
 //
 // Bound by what the L2s fetch again: neighbour spinors and, once per group of
 // columns, links (32^3 x 16 of a 32^3 x 32 field, 12 columns: 11 GB of L2 misses
@@ -929,20 +930,36 @@ struct DwWalk {
 template <int R>
 __global__ void __launch_bounds__(256, 2)
     k_apply_d(BoxGeom g, BlockSpec bs, DwWalk walk, const double2* __restrict__ U, const double2* __restrict__ A,
-              const double2* __restrict__ in, double2* __restrict__ out, int nrhs, int ntl, long rows) {
+              const double2* __restrict__ in, double2* __restrict__ out, int nrhs, int ntl, long rows, int nclear) {
+  // the last nclear workgroups only clear
+  const int nwork = gridDim.x - nclear, c0 = (int)blockIdx.x - nwork;
+  if (c0 >= 0) {
+    clear_rows(g, bs, out, c0 * rows / nclear, (c0 + 1) * rows / nclear);
+    return;
+  }
   const size_t col = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * bs.L[3] * 12;
-  const int x = blockIdx.x % kXcd, nb = gridDim.x / kXcd;
+  const int x = blockIdx.x % kXcd, nb = nwork / kXcd;
   const int* tiles = walk.tile + walk.xoff[x];
   const int ng = (nrhs + R - 1) / R, n = (walk.xoff[x + 1] - walk.xoff[x]) * ng;
+  const bool share = rows && nclear == 0;
   for (int v = blockIdx.x / kXcd; v < n; v += nb) {
     const int tile = ldg(tiles + v / ng), c = (v % ng) * R;
-    if (rows && c == 0) clear_rows(g, bs, out, tile * rows / ntl, (tile + 1) * rows / ntl);
+    if (share && c == 0) clear_rows(g, bs, out, tile * rows / ntl, (tile + 1) * rows / ntl);
     const int s = tile * kTile + (threadIdx.x >> 2);
     if (s >= 2 * g.Vh) continue;   // (the four lanes of a site together)
     dw_site<R>(g, bs, lex_site(g, bs, s), threadIdx.x & 3, U, A, in + c * col, out + c * col, col, min(R, nrhs - c));
   }
 }
 
+// Tiles from which on their workgroups clear the rows outside Gamma on the way:
+// four per CU, enough to keep the stores of the whole chip busy, and the stores
+// then wait for nothing (12 columns, 16 of 32^4's slices, 8192 tiles: 1.49 ms and
+// 1.54 with workgroups of their own; 4 of 64 x 32^3, 2048 tiles: 1.11 and 1.19; 2 of
+// them, 1024 tiles: 1.06 and 1.06).  Fewer cannot clear a large lattice, so that is
+// done beside them (14 x 10 x 8 x 12 of 20 x 12 x 10 x 14, 210 tiles: 70 and 61 us;
+// two slices of 32 x 16^3, 128 tiles: 94 and 78; 4^4 of it, 4 tiles: 1620 and 75).
+constexpr int kShareTiles = 1024;
+constexpr int kClearRows = 4;   // per wave of a workgroup that only clears (1 and 16 rows: the same within 5%)
 hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk, const int* xoff, const double2* U,
                           const double2* A, const double2* in, double2* out, int nrhs, hipStream_t st) {
   if (nrhs < 1 || nrhs > kMaxRhs) return hipErrorInvalidValue;
@@ -958,10 +975,13 @@ hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk
   // (a small box may lie on few XCDs: a workgroup for each of the longest list)
   int longest = 0;
   for (int x = 0; x < kXcd; ++x) longest = xoff[x + 1] - xoff[x] > longest ? xoff[x + 1] - xoff[x] : longest;
-  const int grid = kXcd * (longest * groups < 2048 ? longest * groups : 2048);
+  const int work = kXcd * (longest * groups < 2048 ? longest * groups : 2048);
+  const int nclear =
+      rows && ntl < kShareTiles ? (int)std::min((rows + 4 * kClearRows - 1) / (4 * kClearRows), 65536L) : 0;
 #define DDML_DW(Rv)                                                                                                 \
   case Rv:                                                                                                          \
-    hipLaunchKernelGGL(k_apply_d<Rv>, dim3(grid), dim3(256), 0, st, g, bs, w, U, A, in, out, nrhs, ntl, rows);      \
+    hipLaunchKernelGGL(k_apply_d<Rv>, dim3(work + nclear), dim3(256), 0, st, g, bs, w, U, A, in, out, nrhs, ntl, rows, \
+                       nclear);                                                                                     \
     break;
   switch ((nrhs + groups - 1) / groups) {
     DDML_DW(1)
