@@ -1003,13 +1003,13 @@ hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk
 //   y = x - mu:  -1/2 (1 + gamma_mu) U_mu(y)^dag psi(y)
 // with the time-boundary phase (antiperiodic -1, open: no such hop), on
 // canonical fields and links.  Nearly all of the output is zero: a wavefront takes
-// a row of L3 sites, and one that no coupling reaches is only cleared, in
-// contiguous streaming stores.  The rest go through the quads of lanes of
-// k_apply_d, 16 sites at a time, a lane's site taking the hops that leave Gamma.
-// Bound by the stores: 12 columns of a 32^3 x 32 field, one face of 32^3, 467 us
-// for 2.4 GB, 700 with a thread per site.  (Plain stores 480 us.  A fill in 4 KB
-// workgroups takes 345, but the faces in a launch of their own 100 more, and a
-// launch more is 4 us on a small field.)
+// a run of 16 sites of the field, and one that no coupling reaches is only cleared,
+// in contiguous streaming stores.  The rest go through the quads of lanes of
+// k_apply_d, a lane's site taking the hops that leave Gamma.
+// Bound by the stores: 12 columns of a 32^3 x 32 field, one face of 32^3, 473 us of
+// calls in a row for 2.4 GB, 735 with a thread per site, 485 by rows of L3 sites.
+// (A fill in 4 KB workgroups takes 345 us, but the faces in a launch of their own
+// 100 more, and a launch more is 4 us on a small field.)
 __device__ __forceinline__ const double2* canon_link(const GaugeView& gv, const BlockSpec& bs, size_t site, int t,
                                                      int mu) {
   if (gv.region && t >= gv.r_t0 && t < gv.r_t1)
@@ -1060,7 +1060,46 @@ __device__ __forceinline__ void boundary_site(const GaugeView& gv, const BlockSp
 }
 
 __global__ void __launch_bounds__(256) k_boundary(GaugeView gv, BlockSpec bs, const double2* __restrict__ in,
-                                                  double2* __restrict__ out, unsigned rows, double scale) {
+                                                       double2* __restrict__ out, unsigned runs, double scale) {
+  const int lane = threadIdx.x & 63;
+  const size_t vol = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * bs.L[3] * 12;
+  for (unsigned run = blockIdx.x * 4 + (threadIdx.x >> 6); run < runs; run += gridDim.x * 4) {
+    int x[4];
+    unsigned q = run * 16 + (lane >> 2);
+    double2* const o = out + (size_t)run * 16 * 12;
+#pragma unroll
+    for (int m = 3; m >= 0; --m) {
+      const unsigned r = q / (unsigned)bs.L[m];
+      x[m] = (int)(q - r * bs.L[m]);
+      q = r;
+    }
+    bool inside = true, face = false;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      inside = inside && x[m] >= bs.lo[m] && x[m] < bs.lo[m] + bs.Lb[m];
+      face = face || (bs.Lb[m] != bs.L[m] && (x[m] == bs.lo[m] || x[m] == bs.lo[m] + bs.Lb[m] - 1));
+    }
+    if (!__ballot(inside && face)) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) stg2nt(o + 64 * j + lane, make_double2(0, 0));
+      continue;
+    }
+    double2 v[3] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
+    if (inside && face) boundary_site(gv, bs, x, lane & 3, in + q * vol, scale, v);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) stg2nt(o + (lane >> 2) * 12 + 4 * j + (lane & 3), v[j]);
+  }
+}
+
+// The same by rows of L3 sites, 16 at a time: only x3 differs within a wave, which
+// makes the hops of the other directions uniform branches.  Faster where every row
+// of Gamma has couplings at its ends and fills a wave (16^3 x L3 with all faces cut, 12
+// columns: 88 and 93 us for L3 = 24 and 32, 91 and 99 by runs).  With L3 = 18 it is 87
+// against 80 and with 4 it is 75 against 50.  Without cut ends most rows are only
+// cleared: 96 against 81 with 32, and 128 against 49 on 16 x 32^2 x 2, where a row fills
+// 24 lanes.
+__global__ void __launch_bounds__(256) k_boundary_rows(GaugeView gv, BlockSpec bs, const double2* __restrict__ in,
+                                                       double2* __restrict__ out, unsigned rows, double scale) {
   const int lane = threadIdx.x & 63, L3 = bs.L[3];
   const size_t vol = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * L3 * 12;
   for (unsigned row = blockIdx.x * 4 + (threadIdx.x >> 6); row < rows; row += gridDim.x * 4) {
@@ -1091,11 +1130,18 @@ __global__ void __launch_bounds__(256) k_boundary(GaugeView gv, BlockSpec bs, co
   }
 }
 
+constexpr int kLongRow = 24;
 hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
                            double scale, hipStream_t st) {
   const unsigned rows = (unsigned)nrhs * bs.L[0] * bs.L[1] * bs.L[2];   // (fewer than 2^31 in 288 GB)
-  const unsigned grid = (rows + 3) / 4 < 65536 ? (rows + 3) / 4 : 65536;
-  hipLaunchKernelGGL(k_boundary, dim3(grid), dim3(256), 0, st, gv, bs, in, out, rows, scale);
+  if (bs.L[3] >= kLongRow && bs.Lb[3] != bs.L[3]) {
+    const unsigned grid = std::min((rows + 3) / 4, 65536u);
+    hipLaunchKernelGGL(k_boundary_rows, dim3(grid), dim3(256), 0, st, gv, bs, in, out, rows, scale);
+  } else {
+    const unsigned runs = (unsigned)((size_t)rows * bs.L[3] / 16);   // (every extent is even)
+    const unsigned grid = std::min((runs + 3) / 4, 65536u);
+    hipLaunchKernelGGL(k_boundary, dim3(grid), dim3(256), 0, st, gv, bs, in, out, runs, scale);
+  }
   return hipGetLastError();
 }
 
