@@ -729,7 +729,8 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
 // four waves per SIMD, 1.8 at R = 3, 1.65 at R = 4, 1.58 at R = 6, both with two.
 // The quadrant walk gives 1.72 against 2.03 ms for bands of time slices (R = 4),
 // streaming stores of rows that nothing reads again 1.53 against 1.59.  Measured
-// in all: 1.53 ms; 4.43 when the field was reordered to even-odd tiles and back
+// in all: 1.56 ms; 1.53 with one chain of FMAs through the eight hops, whose sum
+// rounds 40% worse; 4.43 when the field was reordered to even-odd tiles and back
 // around two stencil launches (two gathers, two scatters and three fills, 1.75 ms
 // of it).  On 8 x 4^3 with one column 8 us instead of nine launches of 37.
 struct LexSite {
@@ -841,10 +842,12 @@ __device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, c
 #pragma unroll
         for (int a = 0; a < 3; ++a) h[a] = spin_term(mu, fwd, psi[a], sg1, sg2);
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a) {
+          double2 t = make_double2(0, 0);
 #pragma unroll
-          for (int b = 0; b < 3; ++b)
-            acc[r][a] = fwd ? cmac(acc[r][a], u[3 * a + b], h[b]) : cmacc(acc[r][a], u[3 * b + a], h[b]);
+          for (int b = 0; b < 3; ++b) t = fwd ? cmac(t, u[3 * a + b], h[b]) : cmacc(t, u[3 * b + a], h[b]);
+          acc[r][a] = cadd(acc[r][a], t);
+        }
       }
     }
   // (A psi)_s: this spin's three rows of its chiral 6x6 block.  Spin 0 of the
@@ -1049,12 +1052,14 @@ __device__ __forceinline__ void boundary_site(const GaugeView& gv, const BlockSp
       for (int k = 0; k < 9; ++k) u[k] = ldg2(ug + k);
       quad_to_spin(spin, raw, psi);
 #pragma unroll
-      for (int a = 0; a < 3; ++a) h[a] = cscale(spin_term(mu, fwd, psi[a], sg1, sg2), ph);
+      for (int a = 0; a < 3; ++a) h[a] = spin_term(mu, fwd, psi[a], sg1, sg2);
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+      for (int a = 0; a < 3; ++a) {
+        double2 t = make_double2(0, 0);
 #pragma unroll
-        for (int b = 0; b < 3; ++b)
-          acc[a] = fwd ? cmac(acc[a], u[3 * a + b], h[b]) : cmacc(acc[a], u[3 * b + a], h[b]);
+        for (int b = 0; b < 3; ++b) t = fwd ? cmac(t, u[3 * a + b], h[b]) : cmacc(t, u[3 * b + a], h[b]);
+        acc[a] = cmas(acc[a], t, ph);
+      }
     }
   spin_to_quad(spin, acc, out);
 }
