@@ -657,11 +657,16 @@ __device__ __forceinline__ void quat_times(const double a[4], const double b[4],
   c[3] = a[0] * b[3] + b[0] * a[3] - (a[1] * b[2] - a[2] * b[1]);
 }
 
+// Angles are 2 pi r rounded to FP64, as the documented formula evaluates: sincospi(2 r)
+// skips that rounding and takes 1% less, but then the angles are not those of any
+// other FP64 evaluation of the same random numbers.
+constexpr double kTwoPi = 2.0 * 3.14159265358979323846;
+
 // Kennedy-Pendleton: x0 with density ~ sqrt(1 - x0^2) exp(alpha x0)
 __device__ double kp_sample(double alpha, LinkDraws& d) {
   for (int tries = 0; tries <= 10000; ++tries) {
     const double r1 = d.next(), r2 = d.next(), r3 = d.next(), r4 = d.next();
-    const double c = cospi(2.0 * r2);
+    const double c = cos(kTwoPi * r2);
     const double lam2 = -(log(r1) + c * c * log(r3)) / (2.0 * alpha);
     if (r4 * r4 <= 1.0 - lam2) return 1.0 - 2.0 * lam2;
   }
@@ -692,10 +697,10 @@ __device__ void level1_link(double2 U[9], const double2 A[9], double beta, int n
       if (pass == 0) {
         const double x0 = kp_sample(2.0 * beta * norm / 3.0, d);
         const double rad = sqrt(fmax(0.0, 1.0 - x0 * x0));
-        const double ct = 2.0 * d.next() - 1.0, ph = 2.0 * d.next();
+        const double ct = 2.0 * d.next() - 1.0, ph = kTwoPi * d.next();
         const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
         double sn, cs;
-        sincospi(ph, &sn, &cs);
+        sincos(ph, &sn, &cs);
         const double X[4] = {x0, rad * st * cs, rad * st * sn, rad * ct};
         quat_times(X, vd, R);
       } else {

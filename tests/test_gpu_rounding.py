@@ -1,6 +1,6 @@
-"""GPU: rounding of the FP64 operator and boundary block, against sums in 80-bit numbers.
+"""GPU: rounding of the FP64 operator, boundary block and level-1 update, against 80-bit numbers.
 
-The yardstick is the same arithmetic on the host: every hop a chain of fused
+The yardstick of the sums is the same arithmetic on the host: every hop a chain of fused
 multiply-adds of its own, then one addition per hop.  Its root mean square error is a
 property of that order of operations (a chain through all eight hops, for one, is 40%
 worse), and 200000 components determine it to some 0.2%, so 2% is left.
@@ -19,6 +19,7 @@ DEV = "cuda:0"
 L = (6, 4, 4, 8)
 KAPPA = 0.125   # 2 kappa and its reciprocal are exact
 LD = np.longdouble
+_PI = 4 * np.arctan(LD(1))
 if np.finfo(LD).nmant < 63:
     pytest.skip("long double is no wider than double here", allow_module_level=True)
 
@@ -109,3 +110,70 @@ def test_boundary_block_rounds_like_hops_summed_one_by_one(setup):
     got = ctx.apply_boundary(gid, ctx.set_domain(lo, hi), x, torch.zeros_like(x), 12, scale).cpu().numpy()
     got = got.reshape(full)[:, inside]
     assert _error(got, ref) <= 1.1 * _error(same[0] + 1j * same[1], ref)   # 4600 components: 10%
+
+
+def _philox(ctr, key):
+    x, k0, k1 = list(ctr), key[0], key[1]
+    for _ in range(10):
+        p, q = 0xD2511F53 * x[0], 0xCD9E8D57 * x[2]
+        x = [(q >> 32) ^ x[1] ^ k0, q & 0xFFFFFFFF, (p >> 32) ^ x[3] ^ k1, p & 0xFFFFFFFF]
+        k0, k1 = (k0 + 0x9E3779B9) & 0xFFFFFFFF, (k1 + 0xBB67AE85) & 0xFFFFFFFF
+    return x
+
+
+def _uniforms(site, c1, key):
+    n = 0
+    while True:
+        for w in _philox((site, c1, 0x5EED, n), key):
+            yield (w + 1) / 4294967296.0
+        n += 1
+
+
+def _cold_link(site, beta, key, angle):
+    """A time link of a field of unit links after one heatbath, in 80 bits but for the angles."""
+    draw = _uniforms(site, 0, key)
+    U = np.eye(3).astype(np.clongdouble)
+    for i, j in ((0, 1), (0, 2), (1, 2)):
+        W = U * 6   # all six staples are one
+        q = [(W[i, i].real + W[j, j].real) / 2, (W[i, j].imag + W[j, i].imag) / 2,
+             (W[i, j].real - W[j, i].real) / 2, (W[i, i].imag - W[j, j].imag) / 2]
+        norm = np.sqrt(sum(x * x for x in q))
+        v = [q[0] / norm, -q[1] / norm, -q[2] / norm, -q[3] / norm]
+        while True:
+            r = [next(draw) for _ in range(4)]
+            lam2 = -(np.log(LD(r[0])) + np.cos(angle(r[1])) ** 2 * np.log(LD(r[2]))) / (4 * LD(beta) * norm / 3)
+            if r[3] * r[3] <= 1 - lam2:
+                break
+        x0 = 1 - 2 * lam2
+        rad, ct = np.sqrt(1 - x0 * x0), 2 * LD(next(draw)) - 1
+        ph, st = angle(next(draw)), np.sqrt(1 - ct * ct)
+        a = [x0, rad * st * np.cos(ph), rad * st * np.sin(ph), rad * ct]
+        R = [a[0] * v[0] - a[1] * v[1] - a[2] * v[2] - a[3] * v[3],
+             a[0] * v[1] + v[0] * a[1] - (a[2] * v[3] - a[3] * v[2]),
+             a[0] * v[2] + v[0] * a[2] - (a[3] * v[1] - a[1] * v[3]),
+             a[0] * v[3] + v[0] * a[3] - (a[1] * v[2] - a[2] * v[1])]
+        s, t = R[0] + 1j * R[3], R[2] + 1j * R[1]
+        U[i], U[j] = s * U[i] + t * U[j], np.conj(s) * U[j] - np.conj(t) * U[i]
+    return U
+
+
+def test_level1_angles_are_two_pi_r_in_double_precision():
+    """On unit links the first class of links (time, even sites) depends on its random numbers alone.
+    Rounding 2 pi r to a double moves each by an amount that 80 bits tell; the other roundings
+    of the update are as large, but independent of it."""
+    dims, beta, seed, stream = (4, 4, 4, 4), 6.0, 1234567890123, 3
+    V = int(np.prod(dims))
+    ctx = ddml.Context(dims, ddml.BC_PERIODIC)
+    one = torch.eye(3, dtype=torch.complex128, device=DEV).expand(V, 4, 3, 3).contiguous()
+    torch.cuda.synchronize()
+    gid = ctx.level1_update(ctx.set_gauge(one, KAPPA, 0.0), 0, dims[0], beta, seed, stream, 1, 0)
+    got = ctx.get_gauge(gid, np.zeros((V, 4, 3, 3), complex))[:, 0]
+    ctx.close()
+    key = (seed & 0xFFFFFFFF, (seed >> 32) ^ (stream * 0x85EBCA6B & 0xFFFFFFFF))
+    even = [s for s in range(V) if np.sum(np.unravel_index(s, dims)) % 2 == 0]
+    exact = np.array([_cold_link(s, beta, key, lambda r: 2 * _PI * LD(r)) for s in even])
+    moved = np.array([_cold_link(s, beta, key, lambda r: LD(2.0 * np.pi * r)) for s in even]) - exact
+    assert np.abs(got[even] - exact).max() < 1e-12
+    delta = got[even].astype(np.clongdouble) - exact
+    along = np.sum((np.conj(moved) * delta).real) / np.sum(np.abs(moved) ** 2)
+    assert along > 0.5, along   # one when the angles are rounded, zero when not
