@@ -735,10 +735,9 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
 // of it).  On 8 x 4^3 with one column 8 us instead of nine launches of 37.
 struct LexSite {
   int y[4];
-  int s;        // lexicographic index in the box
-  size_t x;     // canonical site of the host lattice
+  int s;   // lexicographic index in the box
 };
-__device__ __forceinline__ LexSite lex_site(const BoxGeom& g, const BlockSpec& bs, int s) {
+__device__ __forceinline__ LexSite lex_site(const BoxGeom& g, int s) {
   LexSite l;
   l.s = s;
   int r = s;
@@ -746,15 +745,27 @@ __device__ __forceinline__ LexSite lex_site(const BoxGeom& g, const BlockSpec& b
   l.y[2] = r % g.L[2]; r /= g.L[2];
   l.y[1] = r % g.L[1];
   l.y[0] = r / g.L[1];
-  l.x = (((size_t)(bs.lo[0] + l.y[0]) * bs.L[1] + bs.lo[1] + l.y[1]) * bs.L[2] + bs.lo[2] + l.y[2]) * bs.L[3] +
-        bs.lo[3] + l.y[3];
   return l;
+}
+// Where the box lies in a field: lattice and origin.
+struct FieldBox {
+  int L[4], lo[4];
+};
+__host__ __device__ __forceinline__ FieldBox field_box(const BlockSpec& bs) {
+  return {{bs.L[0], bs.L[1], bs.L[2], bs.L[3]}, {bs.lo[0], bs.lo[1], bs.lo[2], bs.lo[3]}};
+}
+__host__ __device__ __forceinline__ size_t field_col(const FieldBox& f) {   // numbers of one column
+  return (size_t)f.L[0] * f.L[1] * f.L[2] * f.L[3] * 12;
+}
+__device__ __forceinline__ size_t field_site(const FieldBox& f, const LexSite& l) {
+  return (((size_t)(f.lo[0] + l.y[0]) * f.L[1] + f.lo[1] + l.y[1]) * f.L[2] + f.lo[2] + l.y[2]) * f.L[3] + f.lo[3] +
+         l.y[3];
 }
 __device__ __forceinline__ int box_stride(const BoxGeom& g, int mu) {
   return (mu < 3 ? g.L[3] : 1) * (mu < 2 ? g.L[2] : 1) * (mu < 1 ? g.L[1] : 1);
 }
-__device__ __forceinline__ long lat_stride(const BlockSpec& bs, int mu) {
-  return (long)(mu < 3 ? bs.L[3] : 1) * (mu < 2 ? bs.L[2] : 1) * (mu < 1 ? bs.L[1] : 1);
+__device__ __forceinline__ long field_stride(const FieldBox& f, int mu) {
+  return (long)(mu < 3 ? f.L[3] : 1) * (mu < 2 ? f.L[2] : 1) * (mu < 1 ? f.L[1] : 1);
 }
 
 __device__ __forceinline__ double2 ldg2(const double2* p) {
@@ -795,13 +806,14 @@ __device__ __forceinline__ double2 spin_term(int mu, bool fwd, double2 psi, doub
 
 // R columns of one site (nr of them in use), this lane's spin
 template <int R>
-__device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, const LexSite& l, int spin,
-                                        const double2* __restrict__ U, const double2* __restrict__ A,
-                                        const double2* __restrict__ in, double2* __restrict__ out, size_t col, int nr) {
+__device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, const FieldBox& fin, const LexSite& l,
+                                        int spin, const double2* __restrict__ U, const double2* __restrict__ A,
+                                        const double2* __restrict__ in, size_t icol, double2* __restrict__ out,
+                                        size_t col, int nr) {
   const int nt = g.ntiles, i = l.s >> 1;
   const int par = (l.y[0] + l.y[1] + l.y[2] + l.y[3]) & 1;
   const double sg1 = spin < 2 ? 1.0 : -1.0, sg2 = (spin == 0 || spin == 3) ? 1.0 : -1.0;
-  const double2* const mine = in + l.x * 12 + spin;   // lane q loads numbers q, q + 4, q + 8
+  const double2* const mine = in + field_site(fin, l) * 12 + spin;   // lane q loads numbers q, q + 4, q + 8
   // all eight hops, by a number that the compiler does not see: in one basic
   // block it moves the loads of later hops up until registers spill
   int hops;
@@ -819,12 +831,12 @@ __device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, c
       const bool fwd = dir == 0;
       const int y = l.y[mu];
       const int step = fwd ? (y + 1 == g.L[mu] ? 1 - g.L[mu] : 1) : (y == 0 ? g.L[mu] - 1 : -1);
-      const double2* src = mine + step * lat_stride(bs, mu) * 12;
+      const double2* src = mine + step * field_stride(fin, mu) * 12;
       double2 raw[R][3], w[3], u[9];
 #pragma unroll
       for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) raw[r][j] = ldg2(src + (r < nr ? r : 0) * col + 4 * j);
+        for (int j = 0; j < 3; ++j) raw[r][j] = ldg2(src + (r < nr ? r : 0) * icol + 4 * j);
       // the link the same way: lane q loads entries q, q + 4 and 8
       const double2* ug = U + (fwd ? lidx(nt, par, mu, 0, i) : lidx(nt, 1 - par, mu, 0, (l.s + step * box_stride(g, mu)) >> 1));
       const double2* uq = ug + 128 * (spin >> 1) + (spin & 1);
@@ -879,7 +891,7 @@ __device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, c
   for (int r = 0; r < R; ++r) {
     double2 raw[3], v[3], w[3], q[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) raw[j] = ldg2(mine + (r < nr ? r : 0) * col + 4 * j);
+    for (int j = 0; j < 3; ++j) raw[j] = ldg2(mine + (r < nr ? r : 0) * icol + 4 * j);
     quad_to_spin(spin, raw, v);
 #pragma unroll
     for (int a = 0; a < 3; ++a) w[a] = quad_xor<1>(v[a]);
@@ -895,7 +907,7 @@ __device__ __forceinline__ void dw_site(const BoxGeom& g, const BlockSpec& bs, c
       q[a] = cscale(cmas(q[a], acc[r][a], -bs.kappa), 1.0 / (2.0 * bs.kappa));
     }
     if (r < nr) {
-      double2* o = out + l.x * 12 + spin + r * col;
+      double2* o = out + field_site(field_box(bs), l) * 12 + spin + r * col;
       double2 t[3];
       spin_to_quad(spin, q, t);
 #pragma unroll
@@ -932,15 +944,16 @@ struct DwWalk {
 };
 template <int R>
 __global__ void __launch_bounds__(256, 2)
-    k_apply_d(BoxGeom g, BlockSpec bs, DwWalk walk, const double2* __restrict__ U, const double2* __restrict__ A,
-              const double2* __restrict__ in, double2* __restrict__ out, int nrhs, int ntl, long rows, int nclear) {
+    k_apply_d(BoxGeom g, BlockSpec bs, FieldBox fin, DwWalk walk, const double2* __restrict__ U,
+              const double2* __restrict__ A, const double2* __restrict__ in, double2* __restrict__ out, int nrhs,
+              int ntl, long rows, int nclear) {
   // the last nclear workgroups only clear
   const int nwork = gridDim.x - nclear, c0 = (int)blockIdx.x - nwork;
   if (c0 >= 0) {
     clear_rows(g, bs, out, c0 * rows / nclear, (c0 + 1) * rows / nclear);
     return;
   }
-  const size_t col = (size_t)bs.L[0] * bs.L[1] * bs.L[2] * bs.L[3] * 12;
+  const size_t col = field_col(field_box(bs)), icol = field_col(fin);
   const int x = blockIdx.x % kXcd, nb = nwork / kXcd;
   const int* tiles = walk.tile + walk.xoff[x];
   const int ng = (nrhs + R - 1) / R, n = (walk.xoff[x + 1] - walk.xoff[x]) * ng;
@@ -950,8 +963,19 @@ __global__ void __launch_bounds__(256, 2)
     if (share && c == 0) clear_rows(g, bs, out, tile * rows / ntl, (tile + 1) * rows / ntl);
     const int s = tile * kTile + (threadIdx.x >> 2);
     if (s >= 2 * g.Vh) continue;   // (the four lanes of a site together)
-    dw_site<R>(g, bs, lex_site(g, bs, s), threadIdx.x & 3, U, A, in + c * col, out + c * col, col, min(R, nrhs - c));
+    dw_site<R>(g, bs, fin, lex_site(g, s), threadIdx.x & 3, U, A, in + c * icol, icol, out + c * col, col,
+               min(R, nrhs - c));
   }
+}
+
+// Gamma's sites of every column of a canonical field, one after the other.
+__global__ void __launch_bounds__(256) k_box_sites(BoxGeom g, FieldBox f, const double2* __restrict__ in,
+                                                   double2* __restrict__ box) {
+  const int n = 2 * g.Vh, s0 = blockIdx.x * 64;
+  in += blockIdx.y * field_col(f);
+  box += ((size_t)blockIdx.y * n + s0) * 12;
+  for (int k = threadIdx.x; k < 64 * 12 && s0 + k / 12 < n; k += 256)
+    box[k] = ldg2(in + field_site(f, lex_site(g, s0 + k / 12)) * 12 + k % 12);
 }
 
 // Tiles from which on their workgroups clear the rows outside Gamma on the way:
@@ -964,8 +988,14 @@ __global__ void __launch_bounds__(256, 2)
 constexpr int kShareTiles = 1024;
 constexpr int kClearRows = 4;   // per wave of a workgroup that only clears (1 and 16 rows: the same within 5%)
 hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk, const int* xoff, const double2* U,
-                          const double2* A, const double2* in, double2* out, int nrhs, hipStream_t st) {
+                          const double2* A, const double2* in, double2* out, int nrhs, double2* copy, hipStream_t st) {
   if (nrhs < 1 || nrhs > kMaxRhs) return hipErrorInvalidValue;
+  FieldBox fin = field_box(bs);
+  if (copy) {   // the input first moves there, Gamma's sites side by side
+    hipLaunchKernelGGL(k_box_sites, dim3((2 * g.Vh + 63) / 64, nrhs), dim3(256), 0, st, g, fin, in, copy);
+    for (int m = 0; m < 4; ++m) fin.L[m] = g.L[m], fin.lo[m] = 0;
+    in = copy;
+  }
   DwWalk w{walk, {}};
   for (int x = 0; x <= kXcd; ++x) w.xoff[x] = xoff[x];
   const int ntl = xoff[kXcd];
@@ -983,8 +1013,8 @@ hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk
       rows && ntl < kShareTiles ? (int)std::min((rows + 4 * kClearRows - 1) / (4 * kClearRows), 65536L) : 0;
 #define DDML_DW(Rv)                                                                                                 \
   case Rv:                                                                                                          \
-    hipLaunchKernelGGL(k_apply_d<Rv>, dim3(work + nclear), dim3(256), 0, st, g, bs, w, U, A, in, out, nrhs, ntl, rows, \
-                       nclear);                                                                                     \
+    hipLaunchKernelGGL(k_apply_d<Rv>, dim3(work + nclear), dim3(256), 0, st, g, bs, fin, w, U, A, in, out, nrhs, ntl,  \
+                       rows, nclear);                                                                               \
     break;
   switch ((nrhs + groups - 1) / groups) {
     DDML_DW(1)

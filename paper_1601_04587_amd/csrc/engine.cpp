@@ -558,16 +558,13 @@ void apply_D(Ctx* c, int gauge_id, int dom_id, const double* in, double* out, in
   const char* a = reinterpret_cast<const char*>(in);
   const char* b = reinterpret_cast<const char*>(out);
   DBuf copy;   // of an input that the output overwrites
-  if (a < b + bytes && b < a + bytes) {
-    copy = DBuf(c->pool.get(), bytes);
-    DDML_HIP(hipMemcpyAsync(copy.p, in, bytes, hipMemcpyDeviceToDevice, st));
-    in = copy.as<double>();
-  }
+  if (a < b + bytes && b < a + bytes) copy = DBuf(c->pool.get(), (size_t)nrhs * 24 * ob->g.Vh * sizeof(double2));
   // (the operator data and the copy may go back to the pool before the kernel
   // has run: every later use of the pool's memory is on the same stream)
   const WalkSet& ws = *ob->walks;
   DDML_HIP(launch_apply_d(ob->g, ob->bs, ws.walk.as<int>() + ws.lex, ws.xlex, ob->U64.as<double2>(), ob->A64.as<double2>(),
-                          reinterpret_cast<const double2*>(in), reinterpret_cast<double2*>(out), nrhs, st));
+                          reinterpret_cast<const double2*>(in), reinterpret_cast<double2*>(out), nrhs,
+                          copy.as<double2>(), st));
 }
 
 // Couplings of D from outside a domain into it; no operator block is needed:

@@ -41,11 +41,12 @@ inline int band_count(int ntiles, int tps, int x) {
   const int lo = (int)((long)x * S / kXcd), hi = (int)((long)(x + 1) * S / kXcd);
   return (hi - lo) * (ntiles / S);
 }
-// out = D_Gamma in on canonical [nrhs][V][12] fields (not overlapping), zero
-// outside Gamma = [bs.lo, bs.lo + bs.Lb); U, A the FP64 links and clover term
-// (walk, xoff: the box's lexicographic 64-site tiles by XCD)
+// out = D_Gamma in on canonical [nrhs][V][12] fields, zero outside Gamma =
+// [bs.lo, bs.lo + bs.Lb); U, A the FP64 links and clover term (walk, xoff: the box's
+// lexicographic 64-site tiles by XCD).  Fields that overlap take a copy of the
+// input's sites in Gamma, nrhs * 24 * g.Vh numbers; else copy is null.
 hipError_t launch_apply_d(const BoxGeom& g, const BlockSpec& bs, const int* walk, const int* xoff, const double2* U,
-                          const double2* A, const double2* in, double2* out, int nrhs, hipStream_t st);
+                          const double2* A, const double2* in, double2* out, int nrhs, double2* copy, hipStream_t st);
 // out = scale * D_{dGamma} in on canonical [nrhs][V][12] fields, Gamma = [bs.lo, bs.lo + bs.Lb)
 hipError_t launch_boundary(const GaugeView& gv, const BlockSpec& bs, const double2* in, double2* out, int nrhs,
                            double scale, hipStream_t st);

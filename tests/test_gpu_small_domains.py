@@ -66,3 +66,37 @@ def test_operator_of_a_small_domain_takes_no_longer_than_the_whole_lattice():
     whole = _median(lambda: ctx.apply_Dw(gid, -1, x, out, 12))
     ctx.close()
     assert small <= whole, (small, whole)
+
+
+@pytest.mark.parametrize("shift", [0, 5, -7, "column", "-column"])
+@pytest.mark.parametrize("L,lo,hi", [((4, 6, 4, 18), (0, 1, 0, 3), (2, 5, 4, 11)), ((4, 4, 4, 4), (0, 0, 0, 0), (4, 4, 4, 4))])
+def test_operator_on_fields_that_overlap(L, lo, hi, shift):
+    """out is in, or lies a few numbers or a column before or behind it."""
+    U = inputs.random_links(L, 7, 0.3)
+    r = np.random.default_rng(4)
+    n, V = 5, int(np.prod(L))
+    psi = r.normal(size=(n, V, 4, 3)) + 1j * r.normal(size=(n, V, 4, 3))
+    ref = oracle.apply_D(U, L, KAPPA, psi, C=oracle.clover_term(U, L, CSW), lo=lo, hi=hi)
+    d = {"column": V * 12, "-column": -V * 12}.get(shift, shift)
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC)
+    gid, dom = ctx.set_gauge(torch.from_numpy(U).to(DEV), KAPPA, CSW), ctx.set_domain(lo, hi)
+    flat = torch.zeros(n * V * 12 + abs(d), dtype=torch.complex128, device=DEV)
+    x, out = flat[max(-d, 0):][:n * V * 12], flat[max(d, 0):][:n * V * 12]
+    x.copy_(torch.from_numpy(psi.reshape(-1)))
+    got = ctx.apply_Dw(gid, dom, x, out, n).cpu().numpy().reshape(psi.shape)
+    ctx.close()
+    assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
+    assert np.all(got[:, ~oracle.domain_mask(L, lo, hi)] == 0)
+
+
+def test_operator_in_place_needs_room_for_the_domain_only():
+    """The pool hands out 2 MiB blocks: field 6 MiB, flag 2, five operator arrays 10, walks 2, and 4 for the
+    domain's two slices of twelve columns.  The whole lattice's would be 20."""
+    L, lo, hi = (16, 8, 8, 8), (7, 0, 0, 0), (9, 8, 8, 8)
+    U = inputs.random_links(L, 7, 0.3)
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC, hbm_budget=34 << 20)
+    gid, dom = ctx.set_gauge(torch.from_numpy(U).to(DEV), KAPPA, CSW), ctx.set_domain(lo, hi)
+    x = torch.randn((12, int(np.prod(L)), 4, 3), dtype=torch.complex128, device=DEV)
+    ref = ctx.apply_Dw(gid, dom, x, torch.zeros_like(x), 12).clone()
+    assert torch.equal(ctx.apply_Dw(gid, dom, x, x, 12), ref)
+    ctx.close()
