@@ -37,26 +37,32 @@ void DevPool::trim() {
   cached_ = 0;
 }
 
+void* DevPool::recycled(size_t r) {
+  std::lock_guard<std::mutex> lk(mu_);
+  auto it = free_.find(r);
+  if (it == free_.end() || it->second.empty()) return nullptr;
+  void* p = it->second.back();
+  it->second.pop_back();
+  cached_ -= r;
+  in_use_ += r;
+  return p;
+}
+
 void* DevPool::alloc(size_t bytes) {
   const size_t r = round(bytes);
-  {
-    std::lock_guard<std::mutex> lk(mu_);
-    auto it = free_.find(r);
-    if (it != free_.end() && !it->second.empty()) {
-      void* p = it->second.back();
-      it->second.pop_back();
-      cached_ -= r;
-      in_use_ += r;
-      return p;
-    }
-    if (in_use_ + r > budget_)
-      throw Error{DDML_ENOMEM, "device memory budget exceeded (" + std::to_string(in_use_ + r) + " > " +
-                                   std::to_string(budget_) + " bytes)"};
+  if (void* p = recycled(r)) return p;
+  if (in_use_ + r > budget_ && reclaim) {
+    reclaim();
+    if (void* p = recycled(r)) return p;
   }
+  if (in_use_ + r > budget_)
+    throw Error{DDML_ENOMEM, "device memory budget exceeded (" + std::to_string(in_use_ + r) + " > " +
+                                 std::to_string(budget_) + " bytes)"};
   if (in_use_ + cached_ + r > budget_) trim();
   void* p = nullptr;
   if (hipMalloc(&p, r) != hipSuccess) {
     (void)hipGetLastError();
+    if (reclaim) reclaim();
     trim();
     if (hipMalloc(&p, r) != hipSuccess) {
       (void)hipGetLastError();
@@ -143,6 +149,10 @@ void ctx_init(Ctx* c, const ddml_lattice* lat, int device, size_t budget) {
     budget = (size_t)(0.9 * (double)fr);
   }
   c->pool.reset(new DevPool(budget));
+  c->pool->reclaim = [c] {   // tile walks that no operator block uses
+    for (auto it = c->walks.begin(); it != c->walks.end();)
+      it = it->second.use_count() == 1 ? c->walks.erase(it) : std::next(it);
+  };
   c->flag = DBuf(c->pool.get(), sizeof(int));
   for (int m = 0; m < 4; ++m) {
     c->full.lo[m] = 0;
@@ -364,10 +374,13 @@ static void fill_spec(Ctx* c, const GaugeRec& g, const DomainRec& d, BlockSpec& 
   geo.twrap = (bs.Lb[0] == bs.L[0] && bs.tbc == DDML_BC_ANTIPERIODIC) ? 1 : 0;
 }
 
-static size_t opblock_bytes(size_t nsites) {  // nsites = 2 * ntiles * 64
+// nsites = 2 * ntiles * 64, with the walks of a shape that has none yet (kWalks
+// of the tiles and one of the 64-site tiles of both parities)
+static size_t opblock_bytes(size_t nsites, bool walks) {
   return DevPool::round(kLinkSlots * nsites * sizeof(double2)) + DevPool::round(kLinkSlots2 * nsites * sizeof(float2)) +
          2 * DevPool::round(kCloverSlots * nsites * sizeof(double2)) +
-         DevPool::round(kCloverSlots * nsites * sizeof(float2)) + 2 * DevPool::round(sizeof(int) * nsites / 128);
+         DevPool::round(kCloverSlots * nsites * sizeof(float2)) +
+         (walks ? DevPool::round(sizeof(int) * (kWalks + 2) * (nsites / 128)) : 0);
 }
 
 static void evict_blocks(Ctx* c) {
@@ -388,7 +401,8 @@ static void build_walk(const BoxGeom& g, int tps, int nrg, int nsub, bool split_
 // The walks of a box: they depend on its extents alone, so every gauge version
 // and every domain of the same extents shares them (building and uploading them
 // again cost 0.1 ms of each new version's operator).  A context that has seen
-// kMaxWalks shapes starts over; blocks keep the walks they hold.
+// kMaxWalks shapes starts over; blocks keep the walks they hold, and those that none
+// holds go when the pool runs out.
 constexpr size_t kMaxWalks = 64;
 static std::shared_ptr<WalkSet> walks_of(Ctx* c, const BoxGeom& g, int tps) {
   const std::array<int, 4> key{g.L[0], g.L[1], g.L[2], g.L[3]};
@@ -452,7 +466,7 @@ std::shared_ptr<OpBlock> opblock(Ctx* c, int gauge_id, int dom_id) {
   ob->tps = (V3h % kTile == 0) ? (int)(V3h / kTile) : 0;
   ob->field = (size_t)12 * ob->ntiles * kTile;
   const size_t ns = (size_t)2 * ob->ntiles * kTile;  // both parities, padded
-  ob->bytes = opblock_bytes(ns);
+  ob->bytes = opblock_bytes(ns, !c->walks.count({ob->g.L[0], ob->g.L[1], ob->g.L[2], ob->g.L[3]}));
   if (!c->pool->fits(ob->bytes)) evict_blocks(c);
   ob->U64 = DBuf(c->pool.get(), kLinkSlots * ns * sizeof(double2));
   ob->U32 = DBuf(c->pool.get(), kLinkSlots2 * ns * sizeof(float2));

@@ -7,6 +7,7 @@
 #include <condition_variable>
 #include <cstdint>
 #include <deque>
+#include <functional>
 #include <array>
 #include <map>
 #include <memory>
@@ -53,8 +54,12 @@ class DevPool {
   size_t cached() const { return cached_; }
   static size_t round(size_t b) { return ((b + (2u << 20) - 1) >> 21) << 21; }
   void trim();  // release cached blocks
+  // called when an allocation does not fit, to give back what the owner only keeps
+  // for later; the allocation is then tried again
+  std::function<void()> reclaim;
 
  private:
+  void* recycled(size_t r);   // a cached block of r bytes, or null
   std::mutex mu_;
   size_t budget_;
   size_t in_use_ = 0;   // bytes handed out

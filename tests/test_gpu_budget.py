@@ -1,0 +1,74 @@
+"""GPU: contexts whose memory budget holds few operator blocks."""
+import numpy as np
+import pytest
+
+import inputs
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+ddml = pytest.importorskip("paper_1601_04587_amd.ddml")
+torch = pytest.importorskip("torch")
+
+DEV = "cuda:0"
+KAPPA, CSW = 0.1340, 1.769
+L = (8, 8, 8, 8)
+MiB = 1 << 20
+
+
+def _boxes(n):
+    """n boxes of different extents."""
+    return [b for b in np.ndindex(4, 4, 4, 4)][1:n + 1]
+
+
+@pytest.fixture
+def field():
+    U = inputs.random_links(L, 7, 0.3)
+    r = np.random.default_rng(4)
+    psi = r.normal(size=(1, int(np.prod(L)), 4, 3)) + 1j * r.normal(size=(1, int(np.prod(L)), 4, 3))
+    return U, psi, torch.from_numpy(U).to(DEV), torch.from_numpy(psi).to(DEV)
+
+
+def _check(ctx, gid, U, psi, x, box):
+    hi = tuple(2 * (k + 1) for k in box)
+    got = ctx.apply_Dw(gid, ctx.set_domain((0, 0, 0, 0), hi), x, torch.zeros_like(x), 1).cpu().numpy()
+    ref = oracle.apply_D(U, L, KAPPA, psi, C=oracle.clover_term(U, L, CSW), lo=(0, 0, 0, 0), hi=hi)
+    assert np.abs(got - ref).max() <= 1e-13 * np.abs(ref).max()
+
+
+def test_more_box_shapes_than_the_budget_holds(field):
+    """A pool block is 2 MiB: field and flag take 6, the operator block of a box with its walks 12, and
+    32 MiB leave room for the walks of seven more shapes."""
+    U, psi, u, x = field
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC, hbm_budget=32 * MiB)
+    gid = ctx.set_gauge(u, KAPPA, CSW)
+    for box in _boxes(14):
+        _check(ctx, gid, U, psi, x, box)
+    ctx.close()
+
+
+def test_walks_of_released_versions_leave_room_for_a_field(field):
+    """After eight shapes the walks take 16 MiB; the flag and five fields take 22 of the 32."""
+    U, psi, u, x = field
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC, hbm_budget=32 * MiB)
+    for box in _boxes(8):
+        gid = ctx.set_gauge(u, KAPPA, CSW)
+        ctx.apply_Dw(gid, ctx.set_domain((0, 0, 0, 0), tuple(2 * (k + 1) for k in box)), x, torch.zeros_like(x), 1)
+        ctx.release_gauge(gid)
+    gids = [ctx.set_gauge(u, KAPPA, CSW) for _ in range(5)]
+    while len(gids) > 1:
+        ctx.release_gauge(gids.pop())
+    _check(ctx, gids[0], U, psi, x, (0, 0, 0, 0))
+    ctx.close()
+
+
+def test_more_box_shapes_than_walks_are_kept_for(field):
+    U, psi, u, x = field
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC)
+    gid = ctx.set_gauge(u, KAPPA, CSW)
+    boxes = _boxes(70)
+    for box in boxes:
+        ctx.apply_Dw(gid, ctx.set_domain((0, 0, 0, 0), tuple(2 * (k + 1) for k in box)), x, torch.zeros_like(x), 1)
+    for box in (boxes[0], boxes[64], boxes[69]):
+        _check(ctx, gid, U, psi, x, box)
+    ctx.close()
