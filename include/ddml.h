@@ -44,7 +44,11 @@
  * hipStream_t (may be NULL for the default stream); work is ordered after
  * what is already queued on it.  Calls that return solver information
  * (solve_domain, propagator_series, solve_batch) block until the result is
- * ready; apply_Dw and apply_eo with on_device=1 only enqueue.
+ * ready; apply_Dw, apply_eo and apply_boundary with on_device=1 only enqueue.
+ * A stream that is being captured into a HIP graph is refused with EDEVICE, and
+ * the capture goes on, except by apply_boundary with on_device=1 and by
+ * contract_nucleon_noalloc, which are captured.  A graph with apply_boundary
+ * reads the gauge version's links: keep the version until its last replay.
  *
  * Errors: every call returns a ddml_status; no exception crosses this
  * boundary.  The message of the most recent failure on a context is returned

@@ -16,22 +16,30 @@ struct ddml_ctx_s {
 namespace {
 
 // Orders the library stream after the caller's stream on entry and the
-// caller's stream after the library stream on exit.
+// caller's stream after the library stream on exit; `run` is the stream to work
+// on.  A stream under capture is refused where the call takes buffers of the
+// library's pool or waits, as a graph would outlive the buffers.  A call that does
+// neither (pool = false) is captured where it is: `run` is then the caller's
+// stream itself.
 struct StreamJoin {
   Ctx* c;
-  hipStream_t user;
-  StreamJoin(Ctx* ctx, void* s) : c(ctx), user((hipStream_t)s) {
+  hipStream_t user, run;
+  bool joined = false;
+  StreamJoin(Ctx* ctx, void* s, bool pool = true) : c(ctx), user((hipStream_t)s), run(ctx->stream) {
     if (user == c->stream) return;   // a call inside a call
-    // every call behind a join uses buffers of the library's pool, which a
-    // captured graph would outlive
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     DDML_HIP(hipStreamIsCapturing(user, &cap));
-    if (cap != hipStreamCaptureStatusNone) throw Error{DDML_EDEVICE, "the caller's stream is being captured"};
+    if (cap != hipStreamCaptureStatusNone) {
+      if (pool) throw Error{DDML_EDEVICE, "the caller's stream is being captured"};
+      run = user;
+      return;
+    }
     DDML_HIP(hipEventRecord(c->join[0], user));
     DDML_HIP(hipStreamWaitEvent(c->stream, c->join[0], 0));
+    joined = true;
   }
   void done() {
-    if (user == c->stream) return;
+    if (!joined) return;
     DDML_HIP(hipEventRecord(c->join[1], c->stream));
     DDML_HIP(hipStreamWaitEvent(user, c->join[1], 0));
   }
@@ -374,10 +382,10 @@ int ddml_apply_boundary(ddml_ctx ctx, int gauge_id, int dom_id, const double* in
     const char* a = reinterpret_cast<const char*>(in);
     const char* b = reinterpret_cast<const char*>(out);
     need(a + bytes <= b || b + bytes <= a, "in and out overlap");
-    StreamJoin sj(c, stream);
+    StreamJoin sj(c, stream, !on_device);
     Staged si = stage_in(c, in, bytes, on_device);
     Staged so = stage_out(c, out, bytes, on_device);
-    apply_boundary(c, gauge_id, dom_id, si.cptr, so.ptr, nrhs, scale, c->stream);
+    apply_boundary(c, gauge_id, dom_id, si.cptr, so.ptr, nrhs, scale, sj.run);
     copy_back(c, out, so, bytes, on_device);
     sj.done();
     return DDML_OK;

@@ -1,0 +1,63 @@
+"""GPU: calls on a stream that is being captured into a graph, and results used on other streams."""
+import numpy as np
+import pytest
+
+import inputs
+
+pytestmark = pytest.mark.gpu
+
+ddml = pytest.importorskip("paper_1601_04587_amd.ddml")
+torch = pytest.importorskip("torch")
+
+DEV = "cuda:0"
+KAPPA, CSW = 0.1340, 1.769
+L, LO, HI = (8, 4, 4, 6), (2, 0, 0, 0), (6, 4, 4, 6)
+
+
+@pytest.fixture
+def setup():
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC)
+    gid = ctx.set_gauge(torch.from_numpy(inputs.random_links(L, 7, 0.3)).to(DEV), KAPPA, CSW)
+    x = torch.randn((3, int(np.prod(L)), 4, 3), dtype=torch.complex128, device=DEV)
+    yield ctx, gid, ctx.set_domain(LO, HI), x
+    ctx.close()
+
+
+def _replays(ctx, gid, dom, x, graph, out):
+    for k in range(4):   # new inputs and eager calls between the replays
+        x.copy_(torch.randn_like(x))
+        ref = ctx.apply_boundary(gid, dom, x, torch.zeros_like(x), 3, -1.0)
+        other = ctx.apply_Dw(gid, dom, x, torch.zeros_like(x), 3)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and bool(torch.isfinite(torch.view_as_real(other)).all())
+
+
+def test_boundary_block_is_captured(setup):
+    ctx, gid, dom, x = setup
+    out = torch.zeros_like(x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.apply_boundary(gid, dom, x, out, 3, -1.0)
+    _replays(ctx, gid, dom, x, graph, out)
+
+
+def test_calls_with_buffers_of_the_pool_refuse_capture_and_leave_it_whole(setup):
+    ctx, gid, dom, x = setup
+    out, sol = torch.zeros_like(x), torch.zeros_like(x)
+    host, res = np.zeros(x.shape, complex), np.zeros(x.shape, complex)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        s = torch.cuda.current_stream().cuda_stream
+        for call in (lambda: ctx.apply_Dw(gid, dom, x, sol, 3), lambda: ctx.apply_eo(gid, dom, x, sol, 3),
+                     lambda: ctx.solve_domain(gid, dom, x, sol, 3), lambda: ctx.trace_g5(x.repeat(4, 1, 1, 1), 1, LO)):
+            with pytest.raises(ddml.DDMLError, match="captured") as e:
+                call()
+            assert e.value.code == ddml.EDEVICE
+        rc = ctx.lib.ddml_apply_boundary(ctx.h, gid, dom, host.ctypes.data, res.ctypes.data, 3, 1.0, 0, s)
+        assert rc == ddml.EDEVICE
+        ctx.apply_boundary(gid, dom, x, out, 3, -1.0)
+    _replays(ctx, gid, dom, x, graph, out)
