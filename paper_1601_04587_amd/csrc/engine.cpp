@@ -1682,7 +1682,7 @@ void time_stencil(Ctx* c, int gauge_id, int dom_id, int nrhs, int prec, int iter
   int splits = want.splits > 0 ? want.splits : tn.splits;
   const int stage = want.stage >= 0 ? want.stage : stage_of(tn.stage, prec, nrhs);
   if (R < 1 || R > 3 || order >= TILE_ORDER_NUM || stage > 1)
-    throw Error{DDML_EINVAL, "R must be 1..3, order 0..3 and stage 0 or 1"};
+    throw Error{DDML_EINVAL, "R must be 1..3, order 0.." + std::to_string(TILE_ORDER_NUM - 1) + " and stage 0 or 1"};
   splits = std::min(splits, (nrhs + R - 1) / R);
   grid = ((grid + kXcd - 1) / kXcd) * kXcd;
   auto ob = opblock(c, gauge_id, dom_id);
