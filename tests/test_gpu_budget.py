@@ -72,3 +72,28 @@ def test_more_box_shapes_than_walks_are_kept_for(field):
     for box in (boxes[0], boxes[64], boxes[69]):
         _check(ctx, gid, U, psi, x, box)
     ctx.close()
+
+
+def _in_use(ctx):
+    ctx.server_start()
+    try:
+        return ctx.stats().hbm_in_use
+    finally:
+        ctx.server_stop()
+
+
+def test_contexts_without_room_for_a_working_copy_are_full():
+    """The paths without a working copy of the links run where not one 2 MiB block is left: field, flag, five
+    operator arrays and walks take 16 MiB on this lattice, field, flag and a level-1 region 6."""
+    dims = (8, 4, 4, 4)
+    U = inputs.random_links(dims, 7, 0.3)
+    x = torch.randn((3, int(np.prod(dims)), 4, 3), dtype=torch.complex128, device=DEV)
+    ctx = ddml.Context(dims, ddml.BC_ANTIPERIODIC, hbm_budget=16 * MiB)
+    ctx.apply_Dw(ctx.set_gauge(torch.from_numpy(U).to(DEV), KAPPA, CSW), ctx.set_domain((2, 0, 1, 0), (6, 4, 3, 4)), x,
+                 torch.zeros_like(x), 3)
+    assert _in_use(ctx) == 16 * MiB
+    ctx.close()
+    ctx = ddml.Context(dims, ddml.BC_ANTIPERIODIC, hbm_budget=6 * MiB)
+    ctx.level1_update(ctx.set_gauge(torch.from_numpy(U).to(DEV), KAPPA, CSW), 1, 6, 6.0, 5, 10, 2, 1)
+    assert _in_use(ctx) == 6 * MiB
+    ctx.close()

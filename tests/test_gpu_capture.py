@@ -61,3 +61,29 @@ def test_calls_with_buffers_of_the_pool_refuse_capture_and_leave_it_whole(setup)
         assert rc == ddml.EDEVICE
         ctx.apply_boundary(gid, dom, x, out, 3, -1.0)
     _replays(ctx, gid, dom, x, graph, out)
+
+
+def test_operator_on_a_side_stream_with_its_memory_taken_right_behind_it():
+    """apply_Dw only enqueues: its version is released, and its memory used for another one, while it runs."""
+    dims = (16, 16, 16, 16)
+    a, b = (torch.from_numpy(inputs.random_links(dims, k, 0.3)).to(DEV) for k in (7, 8))
+    x = torch.randn((12, int(np.prod(dims)), 4, 3), dtype=torch.complex128, device=DEV)
+    ctx = ddml.Context(dims, ddml.BC_ANTIPERIODIC)
+    dom = ctx.set_domain((2, 0, 0, 0), (14, 16, 16, 16))
+    gid = ctx.set_gauge(a, KAPPA, CSW)
+    ref = ctx.apply_Dw(gid, dom, x, torch.zeros_like(x), 12).clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    outs = []
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            out = ctx.apply_Dw(gid, dom, x, torch.zeros_like(x), 12)
+            outs.append(out * 2)   # behind the call on its stream
+        ctx.release_gauge(gid)
+        other = ctx.set_gauge(b, KAPPA, CSW)
+        ctx.apply_Dw(other, dom, x, torch.zeros_like(x), 12)
+        ctx.release_gauge(other)
+        gid = ctx.set_gauge(a, KAPPA, CSW)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, 2 * ref) for o in outs)
+    ctx.close()
