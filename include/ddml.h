@@ -325,9 +325,9 @@ int ddml_contract_nucleon(ddml_ctx ctx, const double* terms, int nlevels, double
 
 /* Allocation-free variant of ddml_contract_nucleon, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc).  It computes the same two arrays (the sum
- * over each sink slice is taken per workgroup of 8 sites first, so results
- * agree with ddml_contract_nucleon to rounding, not bit for bit) and calls no
+ * harnesses that forbid hipMalloc).  It computes the same two arrays with the
+ * same kernels in the same order (the sum over each sink slice is taken per
+ * workgroup of 8 sites first) and calls no
  * hipMalloc, hipFree or allocating library routine: its scratch, the
  * per-workgroup partial sums of nlevels x V/8 complex numbers, lives in a
  * static device array of 16 MiB per device, held until the process ends.

@@ -109,9 +109,6 @@ hipError_t launch_pp(const double2* tx, const double2* ty, size_t V, int nlevels
 }
 
 // ------------------------------------------------------------------ nucleon
-__device__ __forceinline__ double2 cm(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
 __device__ __forceinline__ double2 cadd2(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
 // Sixteen lanes per sink site, lane 4 r + k holding the spin component (k, r) of

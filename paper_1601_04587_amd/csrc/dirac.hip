@@ -723,8 +723,8 @@ __global__ void __launch_bounds__(64 * ((kMaxRhs + R - 1) / R)) k_hop_item(HopIt
 // the same workgroups or by others of the launch (kShareTiles).
 //
 // Bound by what the L2s fetch again: neighbour spinors and, once per group of
-// columns, links (32^3 x 16 of a 32^3 x 32 field, 12 columns: 11 GB of L2 misses
-// with R = 4 at 6.4 TB/s; 4.4 GB is what each input and output takes once).  So
+// columns, links (32^3 x 16 of a 32^3 x 32 field, 12 columns: 8.7 GB read and 2.5 GB
+// written past the L2s, 7.1 TB/s; 4.4 GB is what each input and output takes once).  So
 // more columns per lane are faster and more waves are not: 2.7 ms at R = 1 with
 // four waves per SIMD, 1.8 at R = 3, 1.65 at R = 4, 1.58 at R = 6, both with two.
 // The quadrant walk gives 1.72 against 2.03 ms for bands of time slices (R = 4),
@@ -1339,10 +1339,11 @@ static hipError_t hop_batch_impl(const SlotDesc<T2>* slots, const int* tile_star
   // nw waves cover the columns of a tile; they are split into ng blocks of W
   // waves.  A staged, unsplit workgroup always has the most waves its kernel
   // is built for: those beyond the columns only copy links and clover data,
-  // which one wave does 58 pairs of in turn (M-hat pair of 24^3 x 16 with 1,
-  // 3 and 10 columns: FP32 0.225, 0.142 and 0.217 ms without them, 0.093,
-  // 0.106 and 0.194 with; FP64 0.459, 0.283 and 0.478, then 0.188, 0.216 and
-  // 0.477).
+  // which one wave does 58 pairs of in turn.  M-hat pair without and with them, us:
+  //            FP32, 1, 3, 8 columns        FP64, 1, 3, 8 columns
+  //   4^4      35 22, 27 22, 25 24          38 23, 29 25, 32 30
+  //   16^3 x 8 49 25, 39 28, 38 35          69 33, 49 40, 65 64
+  //   24^3 x 16 222 85, 140 99, 162 152     454 182, 278 212, 382 379
   const int nw = (nrhs + R - 1) / R;
   if (splits < 1 || splits > nw) return hipErrorInvalidValue;
   const int W = stage && splits == 1 ? (kMaxRhs + R - 1) / R : (nw + splits - 1) / splits;

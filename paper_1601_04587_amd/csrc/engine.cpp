@@ -717,8 +717,12 @@ void apply_eo(Ctx* c, int gauge_id, int dom_id, const double* in, double* out, i
 // do unless the choice says otherwise, but for a single column: with several,
 // every wavefront of an unstaged tile reads the links and clover data itself
 // and misses L1, with one there is nothing to share and the 116 KB of LDS
-// leave one tile per CU (M-hat pair of 24^3 x 16 unstaged and staged: 0.148
-// and 0.188 ms with 1 column, 0.267 and 0.198 with 2, 1.35 and 0.55 with 12).
+// leave one tile per CU.  M-hat pair unstaged and staged, us:
+//               1 column   2          3          5         12
+//   4^4         22 23      23 24      26 25      35 29     62 41
+//   8^4         29 27      31 28      35 29      50 35    125 53
+//   16^3 x 8    35 33      44 38      55 40      85 49    178 83
+//   24^3 x 16  132 182    244 194    345 212    515 269  1194 537
 static int stage_of(int stage, int prec, int nrhs) {
   if (prec != DDML_FP64) return 1;
   return stage >= 0 ? stage : (nrhs > 1 ? 1 : 0);

@@ -170,7 +170,7 @@ BoxLinks level1_box(const BlockSpec& bs, int t0, int t1) {
   return bl;
 }
 
-hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const BlockSpec& bs, hipStream_t st) {
+static hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const BlockSpec& bs, hipStream_t st) {
   const int n = sites_of(bl);
   hipLaunchKernelGGL(k_box_copy<true>, dim3((n + 63) / 64), dim3(256), 0, st, gv, nullptr, bs, bl, n);
   return hipGetLastError();
@@ -811,7 +811,7 @@ __global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(4)))
 // without a place for those (staples null, canonical links) a thread adds up its
 // own.
 // On a 16 x 32^3 slab the staples of a class (262144 links) take 80 us, bound by
-// the links they read (0.3 GB at least), and the updates 39 us, bound by the
+// the links they read (0.3 GB at least), and the updates 41 us, bound by the
 // sampler's dependent FP64 operations (three waves per SIMD; four spill: 56 us).
 // In one kernel a class took 193 us from canonical links and 123 us from the
 // working copy, a wavefront for all six staples of its links, or 120 us with the

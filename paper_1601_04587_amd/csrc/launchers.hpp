@@ -133,7 +133,6 @@ size_t box_links_bytes(const BoxLinks& bl);
 // each side of its cut directions; and that a level-1 sweep of a slab reads
 BoxLinks clover_box(const BlockSpec& bs);
 BoxLinks level1_box(const BlockSpec& bs, int t0, int t1);
-hipError_t launch_box_links(const GaugeView& gv, const BoxLinks& bl, const BlockSpec& bs, hipStream_t st);
 // Operator block: FP64 links (5-pair layout) and the two-row FP32 copy (bit 2 of
 // *bad if a link is not SU(3)), clover term and inverse (bit 1 if a block has
 // none).  copy: where to put the working copy of clover_box, or null.
