@@ -169,8 +169,10 @@ __device__ __forceinline__ void msc(double2& acc, double2 a, double2 b) {
   acc.y -= a.y * b.x;
 }
 
-// This lane's part of W_N1 - W_N2 of its site.
-__device__ __forceinline__ double2 nucleon_lane(const double2 (&S)[3][3], int lane) {
+// This lane's part of W_N1 - W_N2 of its site.  The two are summed apart, W_N1 waiting
+// in LDS at *w1: one chain through both rounds a tenth worse, and a second pair of
+// registers spills.
+__device__ __forceinline__ double2 nucleon_lane(const double2 (&S)[3][3], int lane, double2* w1) {
   const bool odd = (lane >> 2) & 1;                  // r mod 2
   const bool minus = ((lane >> 2) ^ lane) & 1;       // k != r mod 2
   double2 W = make_double2(0, 0);
@@ -202,6 +204,9 @@ __device__ __forceinline__ double2 nucleon_lane(const double2 (&S)[3][3], int la
       mac(G, p[b][f], S[c][e]);
       mac(W, St(a, g), G);
     }
+  __builtin_amdgcn_sched_barrier(0);   // (nothing of W_N2 is started ahead of this: it would spill)
+  *w1 = W;
+  W = make_double2(0, 0);
   double2 yo[3][3], zm[3][3], zo[3][3];              // y_{k, 1 - r mod 2}, z_{r mod 2, r}, z_{1 - r mod 2, r}
 #pragma unroll
   for (int a = 0; a < 3; ++a)
@@ -229,14 +234,14 @@ __device__ __forceinline__ double2 nucleon_lane(const double2 (&S)[3][3], int la
       mac(G, yo[c][f], zo[b][e]);
       msc(W, St(a, g), G);
     }
-  return W;
+  return cadd2(*w1, W);
 }
 
 // P[level][block]: the sum over the workgroup's kNucSites sites (they lie in one
 // time slice: every extent is even, so L^3 is a multiple of 8).
 __global__ void __launch_bounds__(128, 2) k_nucleon(const double2* __restrict__ terms, size_t V, int nlevels,
                                                     double2* __restrict__ P) {
-  __shared__ double2 part[2][2];
+  __shared__ double2 part[2][2], w1[128];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int r = (lane >> 2) & 3, k = lane & 3;
   const size_t y = (size_t)blockIdx.x * kNucSites + 4 * w + (lane >> 4);
@@ -279,7 +284,7 @@ __global__ void __launch_bounds__(128, 2) k_nucleon(const double2* __restrict__ 
     if (level + 1 < nlevels) load(level + 1);
     double2 s = make_double2(0, 0);
     if (live) {
-      s = nucleon_lane(S, lane);
+      s = nucleon_lane(S, lane, &w1[threadIdx.x]);
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) {
         s.x += __shfl_xor(s.x, off, 64);
