@@ -48,6 +48,18 @@ void* DevPool::recycled(size_t r) {
   return p;
 }
 
+void* DevPool::fresh(size_t r) {
+  void* p = nullptr;
+  if (hipMalloc(&p, r) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::lock_guard<std::mutex> lk(mu_);
+  sizes_[p] = r;
+  in_use_ += r;
+  return p;
+}
+
 void* DevPool::alloc(size_t bytes) {
   const size_t r = round(bytes);
   if (void* p = recycled(r)) return p;
@@ -59,20 +71,20 @@ void* DevPool::alloc(size_t bytes) {
     throw Error{DDML_ENOMEM, "device memory budget exceeded (" + std::to_string(in_use_ + r) + " > " +
                                  std::to_string(budget_) + " bytes)"};
   if (in_use_ + cached_ + r > budget_) trim();
-  void* p = nullptr;
-  if (hipMalloc(&p, r) != hipSuccess) {
-    (void)hipGetLastError();
+  void* p = fresh(r);
+  if (!p) {
     if (reclaim) reclaim();
     trim();
-    if (hipMalloc(&p, r) != hipSuccess) {
-      (void)hipGetLastError();
-      throw Error{DDML_ENOMEM, "hipMalloc of " + std::to_string(r) + " bytes failed"};
-    }
+    p = fresh(r);
   }
-  std::lock_guard<std::mutex> lk(mu_);
-  sizes_[p] = r;
-  in_use_ += r;
+  if (!p) throw Error{DDML_ENOMEM, "hipMalloc of " + std::to_string(r) + " bytes failed"};
   return p;
+}
+
+void* DevPool::alloc_spare(size_t bytes) {
+  const size_t r = round(bytes);
+  if (void* p = recycled(r)) return p;
+  return in_use_ + cached_ + r > budget_ ? nullptr : fresh(r);
 }
 
 void DevPool::free(void* p) {
@@ -250,16 +262,6 @@ int gauge_region(Ctx* c, int base, int t0, int t1, const double* U, int on_devic
   return id;
 }
 
-// A temporary of the pool, or an empty buffer where it does not fit.
-static DBuf scratch(Ctx* c, size_t bytes) {
-  try {
-    return DBuf(c->pool.get(), bytes);
-  } catch (const Error& e) {
-    if (e.code != DDML_ENOMEM) throw;
-    return DBuf();
-  }
-}
-
 int gauge_level1(Ctx* c, int base, int t0, int t1, double beta, uint64_t seed, uint32_t stream, int nsweeps,
                  int n_or) {
   if (!(beta > 0) || nsweeps < 0 || n_or < 0) throw Error{DDML_EINVAL, "need beta > 0, nsweeps >= 0, n_or >= 0"};
@@ -271,7 +273,7 @@ int gauge_level1(Ctx* c, int base, int t0, int t1, double beta, uint64_t seed, u
   BoxLinks copy = level1_box(bs, t0, t1);
   DBuf work;
   const size_t cb = DevPool::round(box_links_bytes(copy));
-  if (nsweeps > 0) work = scratch(c, cb + level1_staple_bytes(bs, t0, t1));   // without it: swept in place below
+  if (nsweeps > 0) work = DBuf::spare(c->pool.get(), cb + level1_staple_bytes(bs, t0, t1));   // else swept in place
   if (work.p) {
     copy.W = work.as<double2>();
     const GaugeView parent{g.base->as<double2>(), overlay ? overlay->region->as<double2>() : nullptr,
@@ -481,7 +483,7 @@ std::shared_ptr<OpBlock> opblock(Ctx* c, int gauge_id, int dom_id) {
   gv.r_t1 = git->second.r_t1;
   DDML_HIP(hipMemsetAsync(c->flag.p, 0, sizeof(int), c->stream));
   BoxLinks copy = clover_box(ob->bs);
-  DBuf work = scratch(c, box_links_bytes(copy));
+  DBuf work = DBuf::spare(c->pool.get(), box_links_bytes(copy));
   copy.W = work.as<double2>();
   DDML_HIP(launch_build_block(gv, work.p ? &copy : nullptr, ob->bs, ob->g, ob->U64.as<double2>(), ob->U32.as<float2>(),
                               ob->A64.as<double2>(), ob->Ainv64.as<double2>(), ob->Ainv32.as<float2>(),

@@ -44,6 +44,9 @@ class DevPool {
   explicit DevPool(size_t budget) : budget_(budget) {}
   ~DevPool();
   void* alloc(size_t bytes);   // throws Error{ENOMEM}
+  // a block from the cache, or of the budget that neither buffers nor cache hold; else
+  // null: what only saves time takes nothing from anyone
+  void* alloc_spare(size_t bytes);
   void free(void* p);
   bool fits(size_t bytes) const;
   // fits() and the device's free memory (plus this pool's cache) covers it:
@@ -60,6 +63,7 @@ class DevPool {
 
  private:
   void* recycled(size_t r);   // a cached block of r bytes, or null
+  void* fresh(size_t r);      // a new one from the device, or null
   std::mutex mu_;
   size_t budget_;
   size_t in_use_ = 0;   // bytes handed out
@@ -74,6 +78,13 @@ struct DBuf {
   size_t bytes = 0;
   DBuf() = default;
   DBuf(DevPool* pl, size_t b) : pool(pl), p(b ? pl->alloc(b) : nullptr), bytes(b) {}
+  static DBuf spare(DevPool* pl, size_t b) {   // empty where alloc_spare finds nothing
+    DBuf d;
+    d.pool = pl;
+    d.p = pl->alloc_spare(b);
+    d.bytes = d.p ? b : 0;
+    return d;
+  }
   DBuf(const DBuf&) = delete;
   DBuf& operator=(const DBuf&) = delete;
   DBuf(DBuf&& o) noexcept : pool(o.pool), p(o.p), bytes(o.bytes) { o.p = nullptr; }

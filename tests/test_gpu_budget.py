@@ -97,3 +97,26 @@ def test_contexts_without_room_for_a_working_copy_are_full():
     ctx.level1_update(ctx.set_gauge(torch.from_numpy(U).to(DEV), KAPPA, CSW), 1, 6, 6.0, 5, 10, 2, 1)
     assert _in_use(ctx) == 6 * MiB
     ctx.close()
+
+
+def test_working_copies_leave_the_cached_buffers_alone(field):
+    """Field 4 MiB, flag 2, walks 2, level-1 region 4, a block's arrays 16 and two staging buffers of twelve columns
+    20: with 48 MiB all of that stays between calls.  A working copy that had it freed would show in the
+    device's free memory, and cost every later call its buffers."""
+    U, psi, u, x = field
+    ctx = ddml.Context(L, ddml.BC_ANTIPERIODIC, hbm_budget=48 * MiB)
+    gid = ctx.set_gauge(u, KAPPA, CSW)
+    host, out = np.zeros((12, int(np.prod(L)), 4, 3), complex), torch.zeros_like(x)
+    for k in range(5):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        new = ctx.level1_update(gid, 0, 8, 6.0, k, 1, 1, 0)
+        after = [torch.cuda.mem_get_info()[0]]
+        ctx.apply_Dw(new, -1, x, out, 1)
+        torch.cuda.synchronize()
+        after.append(torch.cuda.mem_get_info()[0])
+        ctx.apply_Dw(new, -1, host, host, 12)
+        ctx.release_gauge(new)
+        if k > 1:   # the first rounds find room for working copies before the rest has its buffers
+            assert after == [free, free]
+    ctx.close()
