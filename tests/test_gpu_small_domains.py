@@ -21,8 +21,10 @@ KAPPA, CSW = 0.1340, 1.769
 TOL = 1e-13   # 400 products of order one in FP64: below 400 x 1.1e-16 of the largest value
 
 
-# one tile in rows of 2, 18 and 34 sites; boxes at both ends of the lattice; 36 tiles
+# one tile in rows of 2, 18 and 34 sites; boxes at both ends of the lattice; 36 tiles; 1024 tiles, where
+# the tiles' workgroups start to write the zeros
 @pytest.mark.parametrize("L,lo,hi", [((8, 4, 4, 2), (3, 1, 1, 0), (5, 3, 3, 2)),
+                                     ((10, 16, 16, 32), (1, 0, 0, 0), (9, 16, 16, 32)),
                                      ((4, 6, 4, 18), (0, 0, 0, 0), (2, 2, 2, 2)),
                                      ((4, 2, 6, 34), (2, 0, 4, 31), (4, 2, 6, 33)),
                                      ((6, 8, 12, 12), (1, 0, 0, 0), (3, 8, 12, 12))])
